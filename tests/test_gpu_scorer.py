@@ -86,6 +86,32 @@ def test_scorer_matches_oracle(lib, sc, mode):
     _check(g, r, mode, f"{mode} {sc}")
 
 
+# one case per tile of the matrix products' dispatch (the smallest tile whose workgroups fit one round
+# of 256, from 16 x 32 up, else 128 x 256): M rows, then the tiles of the four products
+TILE_CASES = [
+    (workloads.ScorerConfig(N=1, S=15, K=8), "full"),            # 120: 32x64, 16x32, 32x32, 16x32
+    (workloads.ScorerConfig(N=3, S=9, K=13, H=768, heads=6, F=1152), "full"),  # 351: odd lattice
+    (workloads.ScorerConfig(N=11, S=9, K=13, H=768, heads=6, F=1152), "attn"),  # 1287: 128x128, 64x64
+    (workloads.ScorerConfig(N=11, S=9, K=13, H=768, heads=6, F=1152), "ffn"),   # 64x128, 64x64
+    # 128 x 256 tiles with a ragged last row tile: V^T value by value (L odd) and in quads
+    # (L % 8 == 4), and an output width that ends in half a tile (F = 17 * 128)
+    (workloads.ScorerConfig(N=17, S=9, K=13, F=2176), "attn"),
+    (workloads.ScorerConfig(N=17, S=9, K=13, F=2176), "ffn"),
+    (workloads.ScorerConfig(N=15, S=11, K=12), "attn"),
+]
+
+
+@pytest.mark.parametrize("sc,mode", TILE_CASES,
+                         ids=lambda v: v if isinstance(v, str) else f"N{v.N}S{v.S}K{v.K}H{v.H}F{v.F}")
+def test_scorer_product_tiles(lib, sc, mode):
+    print(f"scorer tiles {mode} N={sc.N} S={sc.S} K={sc.K} H={sc.H} F={sc.F}", flush=True)
+    inp = workloads.make_scorer_inputs(sc)
+    layers = _variant(inp["layers"], mode)
+    g = _gpu(lib, inp["X"], layers, sc)
+    r = osc.scorer_forward(inp["X"].numpy(), _oracle_layers(layers), sc.S, sc.K, sc.heads)
+    _check(g, r, mode, f"tiles {mode} {sc}")
+
+
 def test_scorer_headline_all_requests(lib):
     """The headline shape (64 requests of 15 x 16 candidates, width 1024, two layers) in one call,
     every request checked against the oracle (run eight requests at a time)."""
