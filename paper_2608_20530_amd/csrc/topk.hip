@@ -2,7 +2,8 @@
 // (Sec. 3.2 candidate pool; implementation appendix, "Serving": normalisation and candidate
 // extraction in one kernel).
 //
-// Design (gfx950), one workgroup per row segment, four waves:
+// Many rows take topk_lse_kernel, fewer (or a K large against V) topk_row_kernel, whose notes stand
+// beside it; topk_plan has the rule. topk_lse_kernel (gfx950), one workgroup per row, four waves:
 //  * Three producer waves stream the logits from HBM exactly once with 16-byte non-temporal
 //    buffer loads, in interleaved tiles of 64 lanes x 32 elements (4 KB of bf16); each wave
 //    issues its next tile's loads before it processes the current one.
@@ -28,8 +29,6 @@
 //    its first tile with the K-th largest lane maximum (radix select across lanes).
 //  * Every value the screen derives from T (strictness, the integer bound, the exp reference) is
 //    wave-uniform and kept in scalar registers, so the per-tile control flow is scalar branches.
-//  * Rows split over several workgroups (small N*B) write partial results to the workspace and a
-//    second kernel merges them.
 //  * Every wait (a producer for ring space, the consumer for work) is bounded by a spin limit
 //    passed in at launch. A wait that gives up sets a bit in the status word at the start of the
 //    caller's workspace (the kernel still runs to its end, and that call's outputs are invalid);
@@ -108,11 +107,13 @@ struct TopkShared {
   StagedChunk ring[kProducers][kRing];
 };
 
-__device__ __forceinline__ uint64_t atomic_load_T(TopkShared& sh) {
+template <typename Shared>  // TopkShared, RowShared
+__device__ __forceinline__ uint64_t atomic_load_T(Shared& sh) {
   return uniform64(__hip_atomic_load(&sh.T, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP));
 }
 
-__device__ __forceinline__ void publish_T(TopkShared& sh, uint64_t t) {
+template <typename Shared>
+__device__ __forceinline__ void publish_T(Shared& sh, uint64_t t) {
   if (lane_id() == 0) atomicMax((unsigned long long*)&sh.T, (unsigned long long)t);
 }
 
@@ -428,7 +429,8 @@ struct Consumer {
 };
 
 // Merge a batch of up to 64 keys (one per lane, 0 = none) that beat T into the list.
-__device__ __forceinline__ void consume_batch(Consumer& c, TopkShared& sh, uint64_t v, uint64_t T,
+template <typename Shared>
+__device__ __forceinline__ void consume_batch(Consumer& c, Shared& sh, uint64_t v, uint64_t T,
                                               uint64_t m, int K) {
   const int lane = lane_id();
   const uint64_t before = c.T_own;
@@ -459,8 +461,8 @@ __device__ __forceinline__ void consume_batch(Consumer& c, TopkShared& sh, uint6
 // element position, and merge those that beat the threshold. The threshold has usually risen
 // since the chunks were staged: a lane whose chunk maximum is below its value drops out first,
 // and an element position is skipped when no lane's element reaches that value.
-template <bool BF16>
-__device__ __forceinline__ void consume_chunks(Consumer& c, TopkShared& sh, const u32x4& r,
+template <bool BF16, typename Shared>
+__device__ __forceinline__ void consume_chunks(Consumer& c, Shared& sh, const u32x4& r,
                                                uint32_t id0, uint32_t mask, int K) {
   constexpr int EPC = ElemTraits<BF16>::kEPC;
   uint64_t T = atomic_load_T(sh);
@@ -569,9 +571,9 @@ __device__ __forceinline__ void write_row(uint64_t merged, double lse, int64_t r
 
 template <bool BF16>
 __global__ __launch_bounds__(kTopkWaves * kWave, 4) void topk_lse_kernel(
-    const void* __restrict__ logits, int64_t V, int K, int split, int32_t* __restrict__ ids,
-    float* __restrict__ logp, float* __restrict__ feat, unsigned char* __restrict__ partials,
-    int wait_limit, uint32_t* __restrict__ status) {
+    const void* __restrict__ logits, int64_t V, int K, int32_t* __restrict__ ids,
+    float* __restrict__ logp, float* __restrict__ feat, int wait_limit,
+    uint32_t* __restrict__ status) {
   constexpr int EPC = ElemTraits<BF16>::kEPC;
   constexpr int U = kPerLane / EPC;
   constexpr int TILE = U * kWave;  // chunks per wave tile
@@ -580,12 +582,9 @@ __global__ __launch_bounds__(kTopkWaves * kWave, 4) void topk_lse_kernel(
 
   const int lane = lane_id();
   const int wave = (int)uniform32(threadIdx.x / kWave);
-  const int64_t row = blockIdx.x / split;
-  const int part = blockIdx.x % split;
+  const int64_t row = blockIdx.x;
   const int64_t rowbase = row * V;
-  const int64_t span = (V + split - 1) / split;
-  const int64_t g0 = rowbase + (int64_t)part * span;
-  const int64_t g1 = rowbase + ((int64_t)(part + 1) * span < V ? (int64_t)(part + 1) * span : V);
+  const int64_t g0 = rowbase, g1 = rowbase + V;
 
   if (threadIdx.x == 0) {
     sh.T = 0;
@@ -697,46 +696,385 @@ __global__ __launch_bounds__(kTopkWaves * kWave, 4) void topk_lse_kernel(
     if (sh.cvalid[i]) S += ldexpf(sh.s[i], sh.cref[i] - C);
   const uint64_t merged = cons.L;
 
+  write_row(merged, (log2((double)S) + (double)C) / (double)kLog2eF, row, K, ids, logp, feat);
+}
+
+// ---- whole rows and long segments, no consumer wave -------------------------------------------
+// With fewer rows than the streaming kernel needs to fill the chip, its one consumer wave per
+// segment is what a row waits for: it absorbs about K (1 + ln(len / K)) threshold records one after
+// the other, and cutting the row multiplies the records. Here every wave streams, and the
+// threshold comes from maxima instead of a sorted list: each lane keeps the largest value of each
+// half of its tiles, the workgroup's waves combine theirs in LDS (128 groups, one per lane and
+// half), and the K-th largest group maximum bounds the row's K-th largest value from below. It
+// sits close to it (K of 128 groups hold about 128 ln(128 / (128 - K)) elements: 17 at K = 16, 37
+// at 32, 89 at 64), so few chunks pass. A chunk that passes goes to a list of 64 chunks of the
+// wave's own; only a list that fills up, and at the end every list, is expanded into keys, by
+// which time the threshold drops most of it. Nothing waits but the workgroup's last barriers.
+// A wave takes tiles w, w + NW, ... as in the streaming kernel, with the same exp sums.
+constexpr int kRowList = kWave;  // staged chunks per wave
+constexpr int kRowRagged = 16;   // of them kept free for the segment's ragged ends
+
+template <int NW>
+struct RowShared {
+  uint64_t T;                // best published threshold key (atomic max)
+  uint32_t group[2][kWave];  // order bits of the group maxima (0: none yet)
+  int cref[NW];
+  int cvalid[NW];
+  float s[NW];
+  int count;                 // keys in flat
+  StagedChunk list[NW][kRowList];
+  uint64_t flat[NW * kWave];
+  uint64_t out[kWave];
+};
+
+// One wave's state.
+struct RowWave {
+  Consumer c;        // its sorted key list (empty until a chunk list is expanded)
+  uint32_t top[2];   // order bits of this lane's maxima (halves of the tiles), a lower bound
+  int count;         // (u) staged chunks
+};
+
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Expand the wave's staged chunks (one per lane) into its key list, element position by element
+// position, with the tests of consume_chunks. A loop that reads each element from LDS: inlined
+// once per use, the unrolled form would push the streaming loop's tile buffers out of registers.
+template <bool BF16, int NW>
+__device__ __forceinline__ void row_flush(RowWave& w, RowShared<NW>& sh, int wave, int K) {
+  constexpr int EPC = ElemTraits<BF16>::kEPC;
+  const int lane = lane_id();
+  wave_lds_fence();
+  const StagedChunk& c = sh.list[wave][lane];
+  const uint2 im = *reinterpret_cast<const uint2*>(&c.id0);
+  const uint32_t mask = lane < w.count ? im.y : 0u;
+  w.count = 0;
+  uint64_t T = atomic_load_T(sh);
+  T = uniform64(w.c.T_own > T ? w.c.T_own : T);
+#pragma unroll 1
+  for (int e = 0; e < EPC; ++e) {
+    const float v = BF16 ? __uint_as_float((uint32_t)reinterpret_cast<const uint16_t*>(&c.raw)[e] << 16)
+                         : reinterpret_cast<const float*>(&c.raw)[e];
+    const bool q = ((mask >> e) & 1u) && v >= key_value(T);
+    if (!__ballot(q)) continue;
+    const uint64_t key = q ? make_key(v, im.x + (uint32_t)e) : 0ull;
+    const uint64_t m = __ballot(key > T);
+    if (m) {
+      consume_batch(w.c, sh, key, T, m, K);
+      if (w.c.T_own > T) T = uniform64(w.c.T_own);
+    }
+  }
+  wave_lds_fence();
+}
+
+// Append the chunks of the lanes in m to the wave's list, which has room for them.
+template <int NW>
+__device__ __forceinline__ void row_stage(RowWave& w, RowShared<NW>& sh, int wave, const u32x4& r,
+                                          uint32_t id0, uint32_t mask, uint64_t m) {
+  const int lane = lane_id();
+  if ((m >> lane) & 1u) {
+    const uint32_t off = __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+    StagedChunk& e = sh.list[wave][w.count + (int)off];
+    e.raw = r;
+    *reinterpret_cast<uint2*>(&e.id0) = make_uint2(id0, mask);
+  }
+  w.count += __popcll(m);
+}
+
+// Put this wave's lane maxima into the groups and raise the threshold to the K-th largest group
+// maximum (value part only: lowest possible id) when that is above the published one.
+template <bool BF16, int NW>
+__device__ __forceinline__ void row_raise(RowWave& w, RowShared<NW>& sh, int K) {
+  const int lane = lane_id();
+  uint32_t v[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const uint32_t old = atomicMax(&sh.group[h][lane], w.top[h]);
+    v[h] = old > w.top[h] ? old : w.top[h];
+  }
+  const uint32_t now = (uint32_t)(atomic_load_T(sh) >> 32);
+  auto count = [&](uint32_t t) { return __popcll(__ballot(v[0] >= t)) + __popcll(__ballot(v[1] >= t)); };
+  // order bits of bf16 values have 16 zeros below (ones for negative values): steps of 2^16
+  constexpr int kLow = BF16 ? 16 : 0;
+  if (now == 0xffffffffu || count(now + 1u) < K) return;
+  uint32_t t = 0;
+#pragma unroll
+  for (int bit = 31; bit >= kLow; --bit) {
+    const uint32_t c = t | (1u << bit);
+    if (count(c) >= K) t = c;
+  }
+  t = uniform32(t);
+  // (finite only: a threshold of -inf would say nothing)
+  if (t > now && t > order_bits(-__builtin_inff())) publish_T(sh, (uint64_t)t << 32);
+}
+
+// One tile: screen its chunks against the threshold, stage those that pass, add its exp sums.
+template <bool BF16, int NW>
+__device__ __forceinline__ void row_tile(RowWave& w, Producer& pr, RowShared<NW>& sh, int wave,
+                                         const u32x4 (&raw)[kPerLane / ElemTraits<BF16>::kEPC],
+                                         uint32_t tile_min_id, uint32_t body_end_id, int K,
+                                         bool raise) {
+  constexpr int EPC = ElemTraits<BF16>::kEPC;
+  constexpr int U = kPerLane / EPC;
+  const int lane = lane_id();
+  float x[kPerLane];
+  unpack_tile<BF16>(raw, x);
+  uint64_t T = uniform64(atomic_load_T(sh));
+  uint64_t mk[U];
+#pragma unroll
+  for (int u = 0; u < U; ++u) mk[u] = 0;
+  if (BF16 && !raise && (uint32_t)(T >> 32) > 0x80000000u) {
+    // positive threshold: compare raw bf16 patterns as signed 16-bit integers (see produce_tile)
+    const int tbe = (int)((((uint32_t)(T >> 32) & 0x7fffffffu) >> 16) +
+                          (strict_ok(T, tile_min_id) ? 1u : 0u));
+    i16x2 cm2[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const uint32_t w0 = raw[u][0], w1 = raw[u][1], w2 = raw[u][2], w3 = raw[u][3];
+      cm2[u] = __builtin_elementwise_max(
+          __builtin_elementwise_max(__builtin_bit_cast(i16x2, w0), __builtin_bit_cast(i16x2, w1)),
+          __builtin_elementwise_max(__builtin_bit_cast(i16x2, w2), __builtin_bit_cast(i16x2, w3)));
+    }
+    int hm[2];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      i16x2 m = cm2[h * U / 2];
+#pragma unroll
+      for (int u = h * U / 2 + 1; u < (h + 1) * U / 2; ++u) m = __builtin_elementwise_max(m, cm2[u]);
+      hm[h] = m[0] > m[1] ? (int)m[0] : (int)m[1];
+      const uint32_t o = hm[h] > 0 ? 0x80000000u | ((uint32_t)hm[h] << 16) : 0u;
+      w.top[h] = o > w.top[h] ? o : w.top[h];
+    }
+    if (__ballot((hm[0] > hm[1] ? hm[0] : hm[1]) >= tbe)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int cm = cm2[u][0] > cm2[u][1] ? (int)cm2[u][0] : (int)cm2[u][1];
+        mk[u] = __ballot(cm >= tbe);
+      }
+    }
+  } else {
+    float cm[U], hm[2];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      cm[u] = x[u * EPC];
+#pragma unroll
+      for (int e = 1; e < EPC; ++e) cm[u] = fmaxf(cm[u], x[u * EPC + e]);
+    }
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      hm[h] = cm[h * U / 2];
+#pragma unroll
+      for (int u = h * U / 2 + 1; u < (h + 1) * U / 2; ++u) hm[h] = fmaxf(hm[h], cm[u]);
+      const uint32_t o = order_bits(hm[h]);
+      w.top[h] = o > w.top[h] ? o : w.top[h];
+    }
+    if (raise) {
+      row_raise<BF16, NW>(w, sh, K);
+      T = uniform64(atomic_load_T(sh));
+    }
+    const float tv = key_value(T);
+    const bool strict = strict_ok(T, tile_min_id);
+    const float lm = fmaxf(hm[0], hm[1]);
+    if (strict ? __ballot(lm > tv) : __ballot(lm >= tv)) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) mk[u] = strict ? __ballot(cm[u] > tv) : __ballot(cm[u] >= tv);
+    }
+  }
+  int n = 0;
+#pragma unroll
+  for (int u = 0; u < U; ++u) n += __popcll(mk[u]);
+  // elements past the segment end (the padded last tile) are masked out
+  auto mask_of = [&](uint32_t id0) {
+    const int nv = (int)min(max((int64_t)body_end_id - (int64_t)id0, (int64_t)0), (int64_t)EPC);
+    return (1u << nv) - 1u;
+  };
+  if (n && w.count + n <= kRowList - kRowRagged) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!mk[u]) continue;
+      const uint32_t id0 = tile_min_id + (uint32_t)((u * kWave + lane) * EPC);
+      row_stage(w, sh, wave, raw[u], id0, mask_of(id0), mk[u]);
+    }
+  } else if (n) {
+    // the list is short of room: half a chunk row (32 lanes) at a time, expanding the list
+    // whenever the next half may not fit
+#pragma unroll 1
+    for (int h = 0; h < 2 * U; ++h) {
+      u32x4 r = raw[0];
+      uint64_t m = mk[0];
+#pragma unroll
+      for (int u = 1; u < U; ++u) {
+        r = (h >> 1) == u ? raw[u] : r;
+        m = (h >> 1) == u ? mk[u] : m;
+      }
+      m &= (h & 1) ? 0xffffffff00000000ull : 0x00000000ffffffffull;
+      if (!m) continue;
+      if (w.count + __popcll(m) > kRowList - kRowRagged) row_flush<BF16, NW>(w, sh, wave, K);
+      const uint32_t id0 = tile_min_id + (uint32_t)(((h >> 1) * kWave + lane) * EPC);
+      row_stage(w, sh, wave, r, id0, mask_of(id0), m);
+    }
+  }
+  exp_accumulate<kPerLane>(pr, x);
+}
+
+template <bool BF16, int NW>
+__global__ __launch_bounds__(NW* kWave) void topk_row_kernel(
+    const void* __restrict__ logits, int64_t V, int K, int split, int32_t* __restrict__ ids,
+    float* __restrict__ logp, float* __restrict__ feat, unsigned char* __restrict__ partials) {
+  constexpr int EPC = ElemTraits<BF16>::kEPC;
+  constexpr int U = kPerLane / EPC;
+  constexpr int TILE = U * kWave;  // chunks per wave tile
+  __shared__ RowShared<NW> sh;
+  const int lane = lane_id();
+  const int wave = (int)uniform32(threadIdx.x / kWave);
+  const int64_t row = blockIdx.x / split;
+  const int part = blockIdx.x % split;
+  const int64_t rowbase = row * V;
+  const int64_t span = (V + split - 1) / split;
+  const int64_t g0 = rowbase + (int64_t)part * span;
+  const int64_t g1 = rowbase + ((int64_t)(part + 1) * span < V ? (int64_t)(part + 1) * span : V);
+
+  // body: whole 16-byte chunks inside [g0, g1); head/tail: the ragged elements around it
+  int64_t c_beg = (g0 + EPC - 1) / EPC;
+  int64_t c_end = g1 / EPC;
+  int n_head, n_tail;
+  if (g0 < g1 && c_beg < c_end) {
+    n_head = (int)(c_beg * EPC - g0);
+    n_tail = (int)(g1 - c_end * EPC);
+  } else {
+    c_beg = c_end = 0;
+    n_head = (int)(g1 > g0 ? g1 - g0 : 0);
+    n_tail = 0;
+  }
+  const int64_t nchunks = c_end - c_beg;
+  const int64_t ntiles = (nchunks + TILE - 1) / TILE;
+  const __amdgpu_buffer_rsrc_t rsrc = segment_rsrc(reinterpret_cast<const u32x4*>(logits) + c_beg, nchunks);
+  const uint32_t body_end_id = (uint32_t)(c_end * EPC - rowbase);
+
+  u32x4 ra[U], rb[U];
+  load_tile<BF16>(ra, rsrc, (int64_t)wave * TILE);  // in flight while the shared state is cleared
+  if (threadIdx.x == 0) {
+    sh.T = 0;
+    sh.count = 0;
+  }
+  if (threadIdx.x < 2 * kWave) sh.group[threadIdx.x / kWave][threadIdx.x % kWave] = 0;
+  __syncthreads();
+
+  RowWave w;
+  w.c.L = 0;
+  w.c.T_own = 0;
+  w.top[0] = w.top[1] = 0;
+  w.count = 0;
+  Producer pr;
+  pr.cref = 0;
+  pr.cvalid = 0;
+  pr.s = 0.f;
+  auto step = [&](u32x4 (&cur)[U], u32x4 (&nxt)[U], int64_t t, int i) __attribute__((always_inline)) {
+    load_tile<BF16>(nxt, rsrc, (t + NW) * TILE);
+    if ((t + 1) * TILE > nchunks) pad_tile<BF16>(cur, t * TILE, nchunks);
+    const uint32_t tile_min_id = uniform32((uint32_t)((c_beg + t * TILE) * EPC - rowbase));
+    // the threshold is raised at this wave's tiles 0, 1, 2, 4, 8, ...
+    row_tile<BF16, NW>(w, pr, sh, wave, cur, tile_min_id, body_end_id, K, (i & (i - 1)) == 0);
+  };
+  int i = 0;
+  for (int64_t t = wave; t < ntiles; t += 2 * NW, i += 2) {
+    step(ra, rb, t, i);
+    if (t + NW >= ntiles) break;
+    step(rb, ra, t + NW, i + 1);
+  }
+  if (wave == NW - 1 && n_head + n_tail > 0) {
+    // ragged head/tail elements, one per lane, staged as one-element chunks without a screen
+    float x1[1];
+    int64_t g = -1;
+    if (lane < n_head) g = g0 + lane;
+    else if (lane < n_head + n_tail) g = c_end * EPC + (lane - n_head);
+    uint32_t bits = BF16 ? 0xFF80u : 0xFF800000u;
+    if (g >= 0)
+      bits = BF16 ? (uint32_t)reinterpret_cast<const uint16_t*>(logits)[g]
+                  : reinterpret_cast<const uint32_t*>(logits)[g];
+    x1[0] = __uint_as_float(BF16 ? bits << 16 : bits);
+    const bool live = g >= 0;
+    const uint64_t m = __ballot(live);
+    const uint32_t pad = BF16 ? 0xFF80FF80u : 0xFF800000u;
+    const u32x4 r = u32x4{BF16 ? (bits | 0xFF800000u) : bits, pad, pad, pad};
+    row_stage(w, sh, wave, r, (uint32_t)(g - rowbase), 1u, m);
+    exp_accumulate<1>(pr, x1);
+  }
+  const float ws = wave_sum(pr.s);
+  if (lane == 0) {
+    sh.cref[wave] = pr.cref;
+    sh.cvalid[wave] = pr.cvalid;
+    sh.s[wave] = ws;
+  }
+  __syncthreads();  // the threshold is as high as it gets from maxima
+  row_flush<BF16, NW>(w, sh, wave, K);
+  {
+    // this wave's keys at or above the threshold (T may still rise as the others flush: each sees
+    // a bound that holds)
+    const uint64_t T = atomic_load_T(sh);
+    const bool q = w.c.L != 0ull && w.c.L >= T;
+    const uint64_t m = __ballot(q);
+    int at = 0;
+    if (lane == 0 && m) at = atomicAdd(&sh.count, __popcll(m));
+    at = (int)uniform32((uint32_t)at);
+    if (q)
+      sh.flat[at + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] = w.c.L;
+  }
+  __syncthreads();
+  if (wave != 0) return;
+
+  int C = lane < NW && sh.cvalid[lane] ? sh.cref[lane] : INT_MIN;
+#pragma unroll
+  for (int m = NW / 2; m >= 1; m >>= 1) {
+    const int o = __shfl_xor(C, m, kWave);
+    C = o > C ? o : C;
+  }
+  C = (int)uniform32((uint32_t)C);  // lane 0's: the first NW lanes agree
+  const bool any = C != INT_MIN;
+  if (!any) C = 0;
+  float S = lane < NW && sh.cvalid[lane] ? ldexpf(sh.s[lane], sh.cref[lane] - C) : 0.f;
+  S = wave_sum(S);
+
+  uint64_t merged;
+  const int total = sh.count;
+  if (total <= kWave) {
+    // rank = number of larger keys (keys are distinct)
+    const uint64_t mine = lane < total ? sh.flat[lane] : 0ull;
+    int rank = 0;
+    for (int j = 0; j < total; ++j) rank += sh.flat[j] > mine ? 1 : 0;
+    sh.out[lane] = 0ull;
+    wave_lds_fence();
+    if (lane < total && rank < K) sh.out[rank] = mine;
+    wave_lds_fence();
+    merged = lane < K ? sh.out[lane] : 0ull;
+  } else {
+    merged = 0ull;
+    for (int b = 0; b < total; b += kWave) {
+      const uint64_t v = b + lane < total ? sh.flat[b + lane] : 0ull;
+      merged = b == 0 ? sort_desc64_u64(v) : merge_desc64(merged, sort_desc64_u64(v));
+    }
+    if (lane >= K) merged = 0ull;
+  }
   if (split == 1) {
     write_row(merged, (log2((double)S) + (double)C) / (double)kLog2eF, row, K, ids, logp, feat);
   } else {
     unsigned char* q = partials + ((size_t)row * split + part) * partial_stride(K);
     Partial* hdr = reinterpret_cast<Partial*>(q);
-    uint64_t* keys = reinterpret_cast<uint64_t*>(q + sizeof(Partial));
     if (lane == 0) {
       hdr->cref = C;
-      hdr->cvalid = any;
+      hdr->cvalid = any ? 1 : 0;
       hdr->s = S;
       hdr->pad = 0;
     }
-    if (lane < K) keys[lane] = merged;
+    if (lane < K) reinterpret_cast<uint64_t*>(q + sizeof(Partial))[lane] = merged;
   }
 }
 
-// ---- short row segments --------------------------------------------------------------------
-// Rows split over many workgroups (few rows) leave each workgroup a short segment, where the
-// streaming kernel's fixed costs (producer/consumer set-up, threshold seeding, ring hand-offs)
-// dominate. Segments of at most kSmallSpan logits take this kernel instead and write the same
-// partial record for the merge kernel. Every thread holds 32 logits (element tid + 256 j), all
-// loaded before the first is used. The workgroup reduces the maximum and the exp sum relative to
-// the same integer log2 reference as the streaming kernel.
-// Top-K: a threshold T that at least K of the segment's elements reach, so that its K largest
-// keys all do. At K <= 8 each wave finds the K-th largest of its 64 lane maxima by a bitwise
-// search over their order bits (one ballot per bit) and T is the largest of the four; at larger K
-// (where that leaves more than 64 candidates on random logits) T is the K-th largest of all 256
-// lane maxima (every wave reads them from LDS; four ballots per bit). The elements >= T are the
-// candidates: each lane counts its own, a prefix sum over the wave places them in LDS, and wave 0
-// ranks them (a key's rank is the number of larger candidates; keys are distinct) and writes the
-// K largest in order. When more than 64 elements reach T (exact ties at T, such as a segment that
-// is all -inf), T becomes the workgroup-wide value completed over the ids of the lane maxima (the
-// smallest id holding each) where more lanes than needed hold it, which bounds the candidates by
-// key; more than 64 still take a sort-and-merge loop.
-constexpr int kSmallThreads = 256;
-constexpr int kSmallPer = 32;
-constexpr int64_t kSmallSpan = (int64_t)kSmallThreads * kSmallPer;
-constexpr int kSmallFill = 512;  // workgroups that run at once (two per compute unit)
-constexpr int kSmallWaveK = 8;   // largest K whose first threshold is taken per wave
-
+// ---- merging a row's segments ------------------------------------------------------------------
 // Exclusive prefix sum over the wave of a per-lane count below 64, from one ballot per bit.
 __device__ __forceinline__ int wave_prefix_small(int c) {
   int p = 0;
@@ -747,191 +1085,6 @@ __device__ __forceinline__ int wave_prefix_small(int c) {
                                         __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u)) << bit;
   }
   return p;
-}
-
-// The largest t with at least `need` lanes of the wave holding v >= t.
-__device__ __forceinline__ uint32_t wave_kth_bits(uint32_t v, int need) {
-  uint32_t t = 0;
-#pragma unroll
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t c = t | (1u << bit);
-    if (__popcll(__ballot(v >= c)) >= need) t = c;
-  }
-  return t;
-}
-
-// The largest t such that at least `need` of the workgroup's 256 values v[] (four per lane of
-// every wave, read from LDS, so every wave finds the same t) with on[] set are >= t.
-__device__ __forceinline__ uint32_t block_kth_bits(const uint32_t (&v)[4], const bool (&on)[4],
-                                                   int need) {
-  uint32_t t = 0;
-#pragma unroll
-  for (int bit = 31; bit >= 0; --bit) {
-    const uint32_t c = t | (1u << bit);
-    int n = 0;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) n += __popcll(__ballot(on[i] & (v[i] >= c)));
-    if (n >= need) t = c;
-  }
-  return t;
-}
-
-template <bool BF16>
-__global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(
-    const void* __restrict__ logits, int64_t V, int K, int split,
-    unsigned char* __restrict__ partials) {
-  constexpr int NW = kSmallThreads / kWave;
-  __shared__ uint64_t sCand[kSmallSpan];
-  __shared__ float sMax[NW], sSum[NW];
-  __shared__ uint32_t sKhi[kSmallThreads], sKlo[kSmallThreads];
-  __shared__ int sCount[2];
-  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
-  const int64_t row = blockIdx.x / split;
-  const int part = blockIdx.x % split;
-  const int64_t span = (V + split - 1) / split;
-  const int64_t lo = (int64_t)part * span;
-  const int64_t hi = lo + span < V ? lo + span : V;
-  const int len = (int)(hi > lo ? hi - lo : 0);
-  const int64_t base = row * V + lo;
-  const int rem = len - tid;  // element j of this thread lies in the segment iff 256 j < rem
-  if (tid == 0) sCount[0] = sCount[1] = 0;
-
-  // positions past the segment load the row's first element (in bounds for any segment, even an
-  // empty one) and are masked afterwards, so no load waits behind another
-  float x[kSmallPer];
-  const int64_t rowstart = row * V;
-#pragma unroll
-  for (int j = 0; j < kSmallPer; ++j) {
-    const int64_t g = kSmallThreads * j < rem ? base + tid + kSmallThreads * j : rowstart;
-    if constexpr (BF16)
-      x[j] = __uint_as_float((uint32_t)static_cast<const uint16_t*>(logits)[g] << 16);
-    else
-      x[j] = static_cast<const float*>(logits)[g];
-  }
-  float m = -__builtin_inff();
-#pragma unroll
-  for (int j = 0; j < kSmallPer; ++j) {
-    x[j] = kSmallThreads * j < rem ? x[j] : -__builtin_inff();
-    m = fmaxf(m, x[j]);
-  }
-  const uint32_t khi = rem > 0 ? order_bits(m) : 0u;  // the lane's largest value (0: none)
-  // the threshold: at K <= 8 the largest of the waves' K-th lane maxima (about 4K candidates),
-  // else the K-th largest of all 256 lane maxima (a tighter bound for a costlier search)
-  const bool per_wave = K <= kSmallWaveK;
-  sKhi[tid] = khi;
-  const uint32_t thi = per_wave ? wave_kth_bits(khi, K) : 0u;
-  const float mw = wave_max(m);
-  if (lane == 0) {
-    sMax[wave] = mw;
-    sKlo[wave] = thi;  // the waves' thresholds (sKlo is reused for lane ids only later)
-  }
-  __syncthreads();
-  float M = sMax[0];
-  uint32_t Thi = sKlo[0];
-#pragma unroll
-  for (int w = 1; w < NW; ++w) {
-    M = fmaxf(M, sMax[w]);
-    Thi = sKlo[w] > Thi ? sKlo[w] : Thi;
-  }
-  uint32_t all_hi[4];
-  const bool every[4] = {true, true, true, true};
-#pragma unroll
-  for (int i = 0; i < 4; ++i) all_hi[i] = sKhi[lane + kWave * i];
-  if (!per_wave) Thi = block_kth_bits(all_hi, every, K);
-  const bool valid = M > -__builtin_inff();
-  const int C = valid ? ref_for(M) : 0;
-  const float c = -(float)C;
-  float e = 0.f;
-#pragma unroll
-  for (int j = 0; j < kSmallPer; ++j) e += __builtin_amdgcn_exp2f(fmaf(x[j], kLog2eF, c));
-  e = wave_sum(e);
-  if (lane == 0) sSum[wave] = e;
-
-  // candidates (value, id) >= (Tv, Tlo): value > Tv, or value == Tv and id part >= Tlo (the first
-  // pass takes every id: value >= Tv). The order bits of -0 and +0 are equal, as are the values;
-  // Thi = 0 (fewer than K lanes holding elements, in every wave or in the workgroup, as searched)
-  // makes every element a candidate; the padding (-inf) is told apart by position when Tv is
-  // -inf. Predicates use non-short-circuit operators
-  // so that they compile to mask arithmetic rather than branches.
-  auto place = [&](auto by_id, float Tv, uint32_t Tlo, int slot) {
-    const int lim = Tv == -__builtin_inff() ? rem : kSmallThreads * kSmallPer;
-    auto cand = [&](int j) {
-      const bool in = kSmallThreads * j < lim;
-      if constexpr (decltype(by_id)::value) {
-        const uint32_t idc = 0xFFFFFFFFu - (uint32_t)(lo + tid + kSmallThreads * j);
-        return in & ((x[j] > Tv) | ((x[j] == Tv) & (idc >= Tlo)));
-      } else {
-        return in & (x[j] >= Tv);
-      }
-    };
-    int cnt = 0;
-#pragma unroll
-    for (int j = 0; j < kSmallPer; ++j) cnt += cand(j) ? 1 : 0;
-    int off = wave_prefix_small(cnt);
-    const int wtotal = __shfl(off + cnt, kWave - 1, kWave);
-    int at = 0;
-    if (lane == 0) at = atomicAdd(&sCount[slot], wtotal);
-    off += __shfl(at, 0, kWave);
-#pragma unroll
-    for (int j = 0; j < kSmallPer; ++j)
-      if (cand(j)) sCand[off++] = make_key(x[j], (uint32_t)(lo + tid + kSmallThreads * j));
-  };
-  place(std::false_type{}, Thi ? order_value(Thi) : -__builtin_inff(), 0u, 0);
-  __syncthreads();
-  int total = sCount[0];
-  if (total > kWave) {
-    // the K-th largest of all 256 lane maxima, then, among the lanes holding exactly that value,
-    // the id bits of their keys (the smallest id holding the lane maximum)
-    if (per_wave) Thi = block_kth_bits(all_hi, every, K);
-    int jm = 0;
-#pragma unroll
-    for (int j = kSmallPer - 1; j >= 0; --j) jm = x[j] == m ? j : jm;
-    sKlo[tid] = 0xFFFFFFFFu - (uint32_t)(lo + tid + kSmallThreads * jm);  // every wave read sKlo[w]
-    __syncthreads();
-    uint32_t Tlo = 0;
-    if (Thi != 0) {
-      uint32_t all_lo[4];
-      bool at_t[4];
-      int above = 0;
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        all_lo[i] = sKlo[lane + kWave * i];
-        at_t[i] = all_hi[i] == Thi;
-        above += __popcll(__ballot(all_hi[i] > Thi));
-      }
-      Tlo = block_kth_bits(all_lo, at_t, K - above);
-    }
-    place(std::true_type{}, Thi ? order_value(Thi) : -__builtin_inff(), Tlo, 1);
-    __syncthreads();
-    total = sCount[1];
-  }
-  if (wave != 0) return;
-  float S = 0.f;
-#pragma unroll
-  for (int w = 0; w < NW; ++w) S += sSum[w];
-  unsigned char* q = partials + ((size_t)row * split + part) * partial_stride(K);
-  Partial* hdr = reinterpret_cast<Partial*>(q);
-  uint64_t* keys = reinterpret_cast<uint64_t*>(q + sizeof(Partial));
-  if (lane == 0) {
-    hdr->cref = C;
-    hdr->cvalid = valid ? 1 : 0;
-    hdr->s = valid ? S : 0.f;
-    hdr->pad = 0;
-  }
-  if (total <= kWave) {
-    const uint64_t mine = lane < total ? sCand[lane] : 0ull;
-    int rank = 0;
-    for (int i = 0; i < total; ++i) rank += sCand[i] > mine ? 1 : 0;
-    if (lane < total && rank < K) keys[rank] = mine;
-    if (lane >= total && lane < K) keys[lane] = 0ull;
-  } else {
-    uint64_t L = 0ull;
-    for (int b = 0; b < total; b += kWave) {
-      const uint64_t v = b + lane < total ? sCand[b + lane] : 0ull;
-      L = b == 0 ? sort_desc64_u64(v) : merge_desc64(L, sort_desc64_u64(v));
-    }
-    if (lane < K) keys[lane] = L;
-  }
 }
 
 // One workgroup of four waves per row merges the row's `split` (<= 256) partial results: thread
@@ -1083,24 +1236,37 @@ __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(
   }
 }
 
-// Number of workgroups per row: enough workgroups to fill the chip (about four per CU), but
-// no segment shorter than two workgroup tiles.
-int topk_split(int64_t rows, int64_t V, bool bf16) {
-  const int64_t wg_tile = (int64_t)kProducers * kWave * kPerLane;
-  const int64_t target = 1024;
-  int64_t by_fill = (target + rows - 1) / rows;
-  int64_t by_len = V / (2 * wg_tile);
-  int64_t s = by_fill < by_len ? by_fill : by_len;
-  if (s < by_fill) {
-    // too few rows to fill the chip with streaming segments: when every row's short segments (at
-    // most kSmallSpan logits) run at once, they take the short-segment kernel
-    const int64_t t = (V + kSmallSpan - 1) / kSmallSpan;
-    if (t > 1 && t <= 256 && rows * t <= kSmallFill) s = t;
-  }
-  if (s < 1) s = 1;
-  if (s > 256) s = 256;
-  (void)bf16;
-  return (int)s;
+// Which kernel takes a call, with how many waves per workgroup, and how many workgroups share a row.
+//
+// From 1024 rows on (four per compute unit) the streaming kernel takes whole rows, unless its
+// consumer's ~K (1 + ln(V / K)) records per row weigh more than what the extra wave saves: above
+// K = 16 and below V = 4000 K the row kernel does, four waves each (us, streaming / row kernel:
+// 1024 x 151936 K = 16 52.8 / 55.9, K = 32 56.7 / 62.5, K = 48 75.9 / 72.5; 2048 x 60000 K = 8
+// 45.0 / 49.8, K = 32 82.3 / 66.4; 4000 x 32000 K = 48 186 / 109).
+// Fewer rows take the row kernel: 16 waves a row while every workgroup has a compute unit of its
+// own, else eight, else (bf16, whose exp sums keep the vector units busy) four once eight would
+// need a second round (256 x 151936 K = 16: 20.5 against 30.9 with split rows in the streaming
+// kernel; 512 K = 8: 31.6 against 34.2; 700 x 60000 K = 32: 32.6 against 66.2; 800 x 151936: four
+// waves 54.1, eight 65.7, streaming 64.7; fp32 768 x 131072 K = 32: 69.9, 78.1 with four waves,
+// 87.1), and no more waves than tiles.
+// With fewer rows than compute units a row is split over workgroups of at least one tile per wave
+// (32768 logits); the merge launch costs ~5 us, so two workgroups only pay from 196608 logits
+// on (64 x 151936: four workgroups a row 16.8, one 18.6; 128 x 151936: two 20.2, one 18.8;
+// 100 x 262144: two 23.5, one 24.9; 16 x 151936 K = 8: 14.4, against 14.7 in 19 segments of one
+// 8192-logit tile each).
+struct TopkPlan {
+  int waves;  // 0: the streaming kernel
+  int split;
+};
+
+TopkPlan topk_plan(int64_t rows, int64_t V, int K, bool bf16) {
+  if (rows >= 1024) return {K > 16 && V < (int64_t)4000 * K ? 4 : 0, 1};
+  int64_t split = 256 / rows;
+  if (split > V / 32768) split = V / 32768;
+  if (split < 1 || (split == 2 && V < 196608)) split = 1;
+  int waves = rows * split <= 256 ? 16 : (rows <= 640 || !bf16 ? 8 : 4);
+  while (waves > 4 && (int64_t)(waves / 2) * kWave * kPerLane >= V) waves /= 2;
+  return {waves, (int)split};
 }
 
 bool topk_args_ok(int64_t N, int64_t B, int64_t V, int K) {
@@ -1123,7 +1289,7 @@ inline size_t topk_workspace_need(int64_t rows, int split, int K) {
 
 extern "C" size_t lilicorr_topk_workspace_bytes(int64_t N, int64_t B, int64_t V, int K) {
   if (!topk_args_ok(N, B, V, K) || K > 64 || K > V) return 0;
-  return topk_workspace_need(N * B, topk_split(N * B, V, true), K);
+  return topk_workspace_need(N * B, topk_plan(N * B, V, K, true).split, K);
 }
 
 extern "C" lilicorr_status lilicorr_topk_wait_status(const void* workspace, hipStream_t stream) {
@@ -1156,29 +1322,36 @@ static lilicorr_status topk_launch(const void* logits, lilicorr_dtype dtype, int
     return LILICORR_ERR_ALIGNMENT;
   const bool bf16 = dtype == LILICORR_BF16;
   const int64_t rows = N * B;
-  const int split = topk_split(rows, V, bf16);
+  const TopkPlan plan = topk_plan(rows, V, K, bf16);
+  const int split = plan.split;
   const size_t need = topk_workspace_need(rows, split, K);
   if (!workspace || workspace_bytes < need) return LILICORR_ERR_WORKSPACE;
   if (!aligned16(workspace)) return LILICORR_ERR_ALIGNMENT;
   if (rows * split > 0x7fffffffll) return LILICORR_ERR_UNSUPPORTED;
 
-  dim3 grid((unsigned)(rows * split)), block(kTopkWaves * kWave);
+  const dim3 grid((unsigned)(rows * split));
   uint32_t* status = static_cast<uint32_t*>(workspace);
   unsigned char* ws = static_cast<unsigned char*>(workspace) + kStatusBytes;
-  const int limit = g_wait_limit.load();
-  const bool small = split > 1 && (V + split - 1) / split <= kSmallSpan;
-  if (small && bf16)
-    hipLaunchKernelGGL(topk_small_kernel<true>, grid, dim3(kSmallThreads), 0, stream, logits, V, K,
-                       split, ws);
-  else if (small)
-    hipLaunchKernelGGL(topk_small_kernel<false>, grid, dim3(kSmallThreads), 0, stream, logits, V,
-                       K, split, ws);
-  else if (bf16)
-    hipLaunchKernelGGL(topk_lse_kernel<true>, grid, block, 0, stream, logits, V, K, split, ids, logp,
-                       feat, ws, limit, status);
+  auto row_kernel = [&](auto bf, auto nw) {
+    hipLaunchKernelGGL((topk_row_kernel<decltype(bf)::value, decltype(nw)::value>), grid,
+                       dim3(decltype(nw)::value * kWave), 0, stream, logits, V, K, split, ids, logp,
+                       feat, ws);
+  };
+  auto dispatch = [&](auto bf) {
+    if (plan.waves == 16)
+      row_kernel(bf, std::integral_constant<int, 16>{});
+    else if (plan.waves == 8)
+      row_kernel(bf, std::integral_constant<int, 8>{});
+    else if (plan.waves == 4)
+      row_kernel(bf, std::integral_constant<int, 4>{});
+    else
+      hipLaunchKernelGGL(topk_lse_kernel<decltype(bf)::value>, grid, dim3(kTopkWaves * kWave), 0,
+                         stream, logits, V, K, ids, logp, feat, g_wait_limit.load(), status);
+  };
+  if (bf16)
+    dispatch(std::true_type{});
   else
-    hipLaunchKernelGGL(topk_lse_kernel<false>, grid, block, 0, stream, logits, V, K, split, ids,
-                       logp, feat, ws, limit, status);
+    dispatch(std::false_type{});
   if (launch_status() != LILICORR_OK) return LILICORR_ERR_HIP;
   if (split > 1) {
     hipLaunchKernelGGL(topk_merge_kernel, dim3((unsigned)rows), dim3(kMergeThreads), 0, stream, ws, K, split,

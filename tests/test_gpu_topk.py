@@ -200,6 +200,56 @@ def test_topk_features_ties_and_small_k(lib, K):
     assert (gf[..., :min(K, 10), 2] == 0).all()  # tied with the top: zero gap
 
 
+# ---- the row kernel: waves per workgroup, rows split over workgroups, thresholds from maxima -------
+
+ROW_CASES = [
+    # (rows, V, K, kind): 4, 8 and 16 waves a workgroup by V, ragged ends, K past the group maxima
+    (3, 1, 1, "normal"), (2, 65, 64, "normal"), (5, 2049, 7, "normal"), (3, 4095, 33, "ties"),
+    (3, 8193, 64, "normal"), (2, 16385, 16, "normal"), (2, 32769, 64, "normal"),
+    # split over 3 and 8 workgroups, and two of them from 196608 logits
+    (70, 98310, 2, "normal"), (1, 262147, 50, "ties"), (90, 196609, 3, "normal"),
+    # eight waves (257 rows), four (641 bf16; 1024 with K above V / 4000 and 16)
+    (257, 2100, 9, "normal"), (641, 700, 5, "ties"), (1024, 600, 17, "normal"),
+    # every tile above the last threshold, all the best logits in one lane's groups, one value,
+    # fewer finite logits than K, negative thresholds
+    (2, 20011, 24, "ascending"), (2, 40000, 40, "one lane"), (2, 40001, 64, "equal"),
+    (2, 20000, 12, "few finite"), (2, 33001, 16, "negative"),
+]
+
+
+def _row_logits(rows, V, kind):
+    g = np.random.default_rng(V + rows)
+    x = g.standard_normal((rows, V)).astype(np.float32) * 2
+    if kind == "ties":
+        x = np.round(x * 2) / 2
+    elif kind == "ascending":
+        x = np.linspace(-4, 60, V, dtype=np.float32) + np.zeros((rows, 1), np.float32)
+    elif kind == "one lane":  # lane 5 of every wave's tiles: ids 40 .. 47 of each 512 (bf16)
+        x[:, (np.arange(V) // 8) % 64 == 5] += 20
+    elif kind == "equal":
+        x[:] = -1.5
+    elif kind == "few finite":
+        x[:] = -np.inf
+        x[:, [7, V // 2, V - 1]] = [3.0, -2.0, 0.0]
+    elif kind == "negative":
+        x = -np.abs(x) - 1
+    return torch.from_numpy(x[None])
+
+
+@pytest.mark.parametrize("bf16", [True, False], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("rows,V,K,kind", ROW_CASES)
+def test_topk_row_kernel(lib, rows, V, K, kind, bf16):
+    print(f"row kernel rows={rows} V={V} K={K} {kind} bf16={bf16}", flush=True)
+    x = _row_logits(rows, V, kind)
+    x = x.to(torch.bfloat16) if bf16 else x
+    step = max(1, rows // 24)
+    _check_rows(lib, x, K, range(0, rows, step), f"{kind} V={V} K={K}")
+    # the same call again gives the same bits
+    a, b = _run(lib, x, K), _run(lib, x, K)
+    assert_equal(a[0], b[0], "ids repeat")
+    assert np.array_equal(a[1].view(np.int32), b[1].view(np.int32))
+
+
 # ---- bounded waits: expiry is reported, never silent ---------------------------------------------
 
 def test_topk_wait_expiry_is_reported(lib):
