@@ -16,7 +16,7 @@
 // pass reads (measured at N=256, K=32, d=512: 511 -> 489 us here, 134 -> 102 us for the pair
 // scores that follow).
 //
-// fp32 embeddings: products are no longer exact in bf16, so a plain fp32 FMA kernel is used.
+// fp32 embeddings are split into three bf16 terms too (cand_vectors_f32_kernel).
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -457,69 +457,154 @@ int compute_units() {
   return cached[dev];
 }
 
-constexpr int kF32Rows = 16;
-constexpr int kF32Threads = 256;
+// fp32 embeddings. Each gathered value is split exactly into three bf16 terms like the weights, and
+// eight of the nine products of the terms are summed on the matrix cores (lo x lo, below 2^-30 of
+// the product, is left out), so the error is that of the fp32 sums: 1.1e-7 against 64 bits at
+// d = 64, 2.1e-7 at 192, 4.9e-7 at 1024 (fp32 FMA chains: 1.7e-7, 2.7e-7, 5.9e-7). A workgroup owns
+// 16 RM rows and all d columns of one side, each wave four 16-column blocks, the weights one block
+// at a time through four register buffers as in project_tile_lean. Bound: the weight stream from
+// L2 (3 KB per 8 RM matrix instructions), so two row blocks once they give every compute unit a
+// workgroup and their planes fit; with few rows it is latency, and one row block gives twice the
+// workgroups. (us, the FMA kernel before / this: 1920 rows at d = 192 25 / 9, 4096 at 256 44 / 16,
+// 40000 at 256 385 / 85, 8192 at 512 271 / 65, 4096 at 1024 1122 / 157.)
+constexpr int kF32Planes = 3;
 
-__global__ __launch_bounds__(kF32Threads) void cand_vectors_f32_kernel(
-    const int32_t* __restrict__ ids, const float* __restrict__ E, const float* __restrict__ Wf,
-    int64_t M, int64_t V, int d, float* __restrict__ in_vec, float* __restrict__ out_vec) {
+template <int RM, int MAXT>
+__global__ __launch_bounds__(MAXT) void cand_vectors_f32_kernel(
+    const int32_t* __restrict__ ids, const float* __restrict__ E,
+    const unsigned char* __restrict__ frags, int64_t M, int64_t V, int d, int nbp, int dkp,
+    float* __restrict__ in_vec, float* __restrict__ out_vec) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  float* e = reinterpret_cast<float*>(smem);       // [16][d]
-  float* part = e + kF32Rows * d;                  // [16][256]
-  float* inv = part + kF32Rows * kF32Threads;      // [16]
-  const int side = blockIdx.y;
-  const int64_t r0 = blockIdx.x * (int64_t)kF32Rows;
-  const int tid = threadIdx.x;
-  for (int i = tid; i < kF32Rows * d; i += kF32Threads) {
-    const int r = i / d, c = i % d;
-    const int64_t row = r0 + r;
+  constexpr int ROWS = RM * 16, NB = kNbPerWave;
+  static_assert(NB == 4, "one register buffer per column block");
+  const int dpad = dkp * 32, astride = dpad + 8, plane = ROWS * astride;  // bf16 elements
+  const int side = blockIdx.y, nthreads = blockDim.x, nwaves = nthreads / kWave;
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  const int64_t row0 = blockIdx.x * (int64_t)ROWS;
+  uint16_t* A = reinterpret_cast<uint16_t*>(smem);  // [plane][row][astride]
+  float* ssbuf = reinterpret_cast<float*>(A + kF32Planes * plane);  // [nwaves][ROWS]
+  int32_t* rid = reinterpret_cast<int32_t*>(ssbuf + nwaves * ROWS);  // [ROWS]
+
+  const size_t slice = (size_t)nbp * 1024;
+  const unsigned char* wf =
+      frags + (size_t)side * dkp * 3 * slice + (size_t)wave * NB * 1024 + lane * 16;
+  u32x4 bq[NB][3];
+  auto load = [&](int kb, int nb) {
+    const unsigned char* q = wf + (size_t)kb * 3 * slice + nb * 1024;
+#pragma unroll
+    for (int t = 0; t < 3; ++t) bq[nb][t] = *reinterpret_cast<const u32x4*>(q + t * slice);
+  };
+  load(0, 0);  // in flight during the gather
+  load(0, 1);
+  load(0, 2);
+  for (int r = tid; r < ROWS; r += nthreads) {
+    const int64_t row = row0 + r;
     const int32_t id = row < M ? ids[row] : -1;
-    e[i] = (id >= 0 && id < V) ? E[(int64_t)id * d + c] : 0.f;  // outside [0, V): zero row
+    rid[r] = (id >= 0 && id < V) ? id : -1;
   }
   __syncthreads();
-  const float* W = Wf + (size_t)side * d * d;
-  float u[4][kF32Rows];
-  float ss[kF32Rows];
+  // four values at a time, eight loads in flight per thread; zero past d, past M and for ids
+  // outside [0, V)
+  const int cpr = dpad / 4;
+  for (int i0 = tid; i0 < ROWS * cpr; i0 += 8 * nthreads) {
+    f32x4 v[8];
 #pragma unroll
-  for (int r = 0; r < kF32Rows; ++r) ss[r] = 0.f;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int j = tid + q * kF32Threads;
-#pragma unroll
-    for (int r = 0; r < kF32Rows; ++r) u[q][r] = 0.f;
-    if (j < d) {
-      // unrolled so that several weight loads are in flight at once (d is a multiple of 16)
-#pragma unroll 16
-      for (int i = 0; i < d; ++i) {
-        const float w = W[(int64_t)i * d + j];
-#pragma unroll
-        for (int r = 0; r < kF32Rows; ++r) u[q][r] = fmaf(e[r * d + i], w, u[q][r]);
+    for (int q = 0; q < 8; ++q) {
+      const int i = i0 + q * nthreads;
+      v[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+      if (i < ROWS * cpr) {
+        const int r = i / cpr, c = (i - r * cpr) * 4;
+        const int32_t id = rid[r];
+        if (id >= 0 && c < d) v[q] = *reinterpret_cast<const f32x4*>(E + (int64_t)id * d + c);
       }
+    }
 #pragma unroll
-      for (int r = 0; r < kF32Rows; ++r) ss[r] = fmaf(u[q][r], u[q][r], ss[r]);
+    for (int q = 0; q < 8; ++q) {
+      const int i = i0 + q * nthreads;
+      if (i < ROWS * cpr) {
+        const int r = i / cpr, c = (i - r * cpr) * 4;
+#pragma unroll
+        for (int t = 0; t < kF32Planes; ++t) {
+          uint32_t w[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) w[e] = split_term(v[q][e], t);
+          *reinterpret_cast<uint2*>(A + t * plane + r * astride + c) =
+              make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
+        }
+      }
     }
   }
-#pragma unroll
-  for (int r = 0; r < kF32Rows; ++r) part[r * kF32Threads + tid] = ss[r];
   __syncthreads();
-  if (tid < kF32Rows) {
-    float t = 0.f;
-    for (int i = 0; i < kF32Threads; ++i) t += part[tid * kF32Threads + i];
-    inv[tid] = t > 0.f ? 1.0f / sqrtf(t) : 0.f;
+
+  f32x4 acc[RM][NB];
+#pragma unroll
+  for (int mb = 0; mb < RM; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int kb = 0; kb < dkp; ++kb) {
+    bf16x8 a[kF32Planes][RM];
+    const int kcol = kb * 32 + (lane >> 4) * 8;
+#pragma unroll
+    for (int t = 0; t < kF32Planes; ++t)
+#pragma unroll
+      for (int mb = 0; mb < RM; ++mb)
+        a[t][mb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(
+                                                  A + t * plane + (mb * 16 + (lane & 15)) * astride + kcol));
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      if (nb == 0) load(kb, 3);
+      else if (kb + 1 < dkp) load(kb + 1, nb - 1);
+      __builtin_amdgcn_sched_barrier(0);
+      // smallest products first
+#pragma unroll
+      for (int o = 3; o >= 0; --o)
+#pragma unroll
+        for (int t = 0; t < kF32Planes; ++t)
+          if (o - t >= 0 && o - t < 3)
+#pragma unroll
+            for (int mb = 0; mb < RM; ++mb)
+              acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                  a[t][mb], __builtin_bit_cast(bf16x8, bq[nb][o - t]), acc[mb][nb], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
   }
+  row_sumsq<RM, NB>(acc, ssbuf + wave * ROWS, lane);
   __syncthreads();
   float* out = side == 0 ? in_vec : out_vec;
+  const int col0 = wave * NB * 16 + (lane & 15);
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int j = tid + q * kF32Threads;
-    if (j < d) {
+  for (int mb = 0; mb < RM; ++mb) {
 #pragma unroll
-      for (int r = 0; r < kF32Rows; ++r) {
-        const int64_t row = r0 + r;
-        if (row < M) out[row * d + j] = u[q][r] * inv[r];
+    for (int i = 0; i < 4; ++i) {
+      const int rl = mb * 16 + (lane >> 4) * 4 + i;
+      float tot = 0.f;
+      for (int g = 0; g < nwaves; ++g) tot += ssbuf[g * ROWS + rl];
+      const float inv = tot > 0.f ? 1.0f / sqrtf(tot) : 0.f;
+      const int64_t r = row0 + rl;
+      if (r < M) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          if (col0 + nb * 16 < d)
+            __builtin_nontemporal_store(acc[mb][nb][i] * inv, &out[r * d + col0 + nb * 16]);
       }
     }
   }
+}
+
+template <int RM, int MAXT>
+void launch_vectors_f32(const int32_t* ids, const float* E, const unsigned char* p, int64_t M,
+                        int64_t V, int d, const VecGeom& g, float* in_vec, float* out_vec,
+                        hipStream_t stream) {
+  constexpr int ROWS = RM * 16;
+  const size_t lds = (size_t)kF32Planes * ROWS * (g.dkp * 32 + 8) * 2 +
+                     (size_t)g.waves * ROWS * sizeof(float) + ROWS * sizeof(int32_t);
+  static const hipError_t attr = hipFuncSetAttribute(
+      reinterpret_cast<const void*>(cand_vectors_f32_kernel<RM, MAXT>),
+      hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+  (void)attr;
+  hipLaunchKernelGGL((cand_vectors_f32_kernel<RM, MAXT>), dim3((unsigned)((M + ROWS - 1) / ROWS), 2),
+                     dim3(g.waves * kWave), lds, stream, ids, E, p, M, V, d, g.nbp, g.dkp, in_vec,
+                     out_vec);
 }
 
 bool vec_d_ok(int d) { return d >= 16 && d <= 1024 && d % 16 == 0; }
@@ -607,16 +692,20 @@ extern "C" lilicorr_status lilicorr_candidate_vectors(const int32_t* ids, const 
                          M, V, d, g.nbp, g.dkp, in_vec, out_vec);
     }
   } else {
-    const int64_t nblk = (M + kF32Rows - 1) / kF32Rows;
-    if (nblk > 0x7fffffffll) return LILICORR_ERR_UNSUPPORTED;
-    const size_t lds = ((size_t)kF32Rows * d + kF32Rows * kF32Threads + kF32Rows) * sizeof(float);
-    static const hipError_t attr_f32 = hipFuncSetAttribute(
-        reinterpret_cast<const void*>(cand_vectors_f32_kernel),
-        hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    (void)attr_f32;
-    hipLaunchKernelGGL(cand_vectors_f32_kernel, dim3((unsigned)nblk, 2), dim3(kF32Threads), lds,
-                       stream, ids, static_cast<const float*>(E),
-                       reinterpret_cast<const float*>(p + frag_bytes(d)), M, V, d, in_vec, out_vec);
+    const VecGeom g = vec_geom(d, M);
+    const float* e32 = static_cast<const float*>(E);
+    if ((M + 15) / 16 > 0x7fffffffll) return LILICORR_ERR_UNSUPPORTED;
+    // two row blocks once they give every compute unit a workgroup (above d = 768 their three
+    // planes do not fit in LDS)
+    const bool two = (M + 31) / 32 * 2 >= 256 && d <= 768;
+    if (g.waves > 8 && two)
+      launch_vectors_f32<2, 1024>(ids, e32, p, M, V, d, g, in_vec, out_vec, stream);
+    else if (g.waves > 8)
+      launch_vectors_f32<1, 1024>(ids, e32, p, M, V, d, g, in_vec, out_vec, stream);
+    else if (two)
+      launch_vectors_f32<2, 512>(ids, e32, p, M, V, d, g, in_vec, out_vec, stream);
+    else
+      launch_vectors_f32<1, 512>(ids, e32, p, M, V, d, g, in_vec, out_vec, stream);
   }
   return launch_status();
 }

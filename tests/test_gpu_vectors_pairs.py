@@ -105,6 +105,35 @@ def test_vectors_persistent_tiles(lib, d, N, B, K):
     assert (giv[0] == 0).all() and (giv[M - 1] == 0).all()
 
 
+@pytest.mark.parametrize("d,M", [(16, 15), (80, 17), (528, 33), (1024, 16),    # one row block
+                                 (48, 4065), (512, 4100), (560, 4100), (768, 4079),  # two
+                                 (784, 4100)])
+def test_vectors_f32_rows(lib, d, M):
+    """fp32 embeddings: one and two 16-row blocks per workgroup, up to and above 512 threads, ragged
+    rows, ids outside the table. The sums are fp32 over exact products of bf16 terms: the bound is
+    the mean error of d fp32 additions, sqrt(d) 2^-24 of a unit vector's norm, with a factor 4."""
+    V = 500
+    print(f"vectors f32 d={d} M={M}", flush=True)
+    rng = np.random.default_rng(d + M)
+    E = (rng.standard_normal((V, d)) * 0.05).astype(np.float32)
+    E[7] = 0.0
+    W_in = (rng.standard_normal((d, d)) / np.sqrt(d)).astype(np.float32)
+    W_out = (rng.standard_normal((d, d)) / np.sqrt(d)).astype(np.float32)
+    ids = rng.integers(0, V, size=M).astype(np.int32)
+    ids[0], ids[3], ids[M - 1] = 7, -1, V
+    giv, gov = _gpu_vectors(lib, ids[None, :, None], torch.from_numpy(E), torch.from_numpy(W_in),
+                            torch.from_numpy(W_out))
+    giv, gov = giv.reshape(M, d), gov.reshape(M, d)
+    for r in (0, 3, M - 1):
+        assert (giv[r] == 0).all() and (gov[r] == 0).all(), f"row {r}"
+    for g, W in ((giv, W_in), (gov, W_out)):
+        ok = np.flatnonzero((ids >= 0) & (ids < V) & (ids != 7))
+        u = E[ids[ok]].astype(np.float64) @ W.astype(np.float64)
+        u /= np.linalg.norm(u, axis=1, keepdims=True)
+        err = np.linalg.norm(g[ok] - u, axis=1).max()
+        assert err <= 4 * np.sqrt(d) * 2.0 ** -24, f"d={d}: row error {err:.2e}"
+
+
 def test_vectors_identity_weights(lib):
     d, V = 64, 50
     rng = np.random.default_rng(9)
