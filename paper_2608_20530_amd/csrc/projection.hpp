@@ -24,6 +24,16 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
+// Term 0, 1 or 2 (hi, mid, lo) of the exact three-way bf16 split of an fp32 value.
+__device__ __forceinline__ uint16_t split_term(float w, int term) {
+  float hi = __uint_as_float(__float_as_uint(w) & 0xffff0000u);
+  float r1 = w - hi;  // exact: the low 16 significand bits of w
+  float mid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
+  float r2 = r1 - mid;  // exact, at most 8 significant bits: a bf16 value
+  float t = term == 0 ? hi : (term == 1 ? mid : r2);
+  return (uint16_t)(__float_as_uint(t) >> 16);
+}
+
 // The packed layout pads the output columns to whole groups of kNbPerWave 16-column blocks (the
 // candidate-vector kernel's waves own one group each); a kernel may give its waves fewer blocks
 // (NB, a divisor of kNbPerWave) and so run more waves over the same layout.

@@ -24,18 +24,10 @@
 #include "common.hpp"
 #include "lilicorr.h"
 #include "projection.hpp"
+#include "vectors_cols.hpp"
 
 namespace lilicorr {
 namespace {
-
-__device__ __forceinline__ uint16_t split_term(float w, int term) {
-  float hi = __uint_as_float(__float_as_uint(w) & 0xffff0000u);
-  float r1 = w - hi;  // exact: the low 16 significand bits of w
-  float mid = __uint_as_float(__float_as_uint(r1) & 0xffff0000u);
-  float r2 = r1 - mid;  // exact, at most 8 significant bits: a bf16 value
-  float t = term == 0 ? hi : (term == 1 ? mid : r2);
-  return (uint16_t)(__float_as_uint(t) >> 16);
-}
 
 __global__ void pack_weights_kernel(const float* __restrict__ W_in, const float* __restrict__ W_out,
                                     int d, int nbp, int dkp, uint16_t* __restrict__ frags,
@@ -607,6 +599,43 @@ void launch_vectors_f32(const int32_t* ids, const float* E, const unsigned char*
                      out_vec);
 }
 
+// Which kernels take a call. Whole rows per workgroup cost the latency of a side's whole weights
+// however few rows there are (bf16: 17 us at d = 256, 25 at 512, 68 at 1024; fp32 9, 17 and 70), so
+// while the tiles of vectors_split_kernel fit one round of compute units the smallest such tile is
+// taken (us, bf16, with the norm pass: 128 rows 6.1, 6.5 and 8.9; 512 rows at d = 512 9.6, at 1024
+// 17.2; 4096 rows at 256 16.4 against 18.3), for fp32 from d = 256 on, there up to 512 rows (1024
+// rows at 256: 11 against 9.9). Above d = 768 the 1024-thread whole-row workgroups lose to 128 x 128
+// tiles at any row count (d = 1024, 2048 rows 37 against 63, 4096 64 against 72, 16384 236 against
+// 269); between 512 and 768 only while one round holds the tiles (4096 rows at 768: 48 against 41).
+enum { kVecRows = 0, kVec16x32, kVec32x32, kVec32x64, kVec64x64, kVec64x128, kVecTiles };
+
+int vec_kernel(int64_t M, int64_t V, int d, bool f32) {
+  if (V * d * (f32 ? 4 : 2) >= ((int64_t)1 << 31) || M >= ((int64_t)1 << 31)) return kVecRows;
+  auto fits = [&](int bm, int bn) { return (M + bm - 1) / bm * ((d + bn - 1) / bn) * 2 <= 256; };
+  if (!f32 || d > 256 || (d == 256 && M <= 512)) {
+    if (fits(16, 32)) return kVec16x32;
+    if (fits(32, 32)) return kVec32x32;
+    if (fits(32, 64)) return kVec32x64;
+    if (fits(64, 64)) return kVec64x64;
+    if (fits(64, 128)) return kVec64x128;
+  }
+  if (!f32 && (d > 768 || (d > 512 && fits(128, 128)))) return kVecTiles;
+  return kVecRows;
+}
+
+template <bool F32>
+void launch_vectors_spread(int kernel, const ColsArgs& a, hipStream_t stream) {
+  switch (kernel) {
+    case kVec16x32: launch_vectors_split<F32, 1, 2, 1, 1, 2>(a, stream); break;
+    case kVec32x32: launch_vectors_split<F32, 2, 2, 1, 1, 2>(a, stream); break;
+    case kVec32x64: launch_vectors_split<F32, 2, 4, 1, 1, 2>(a, stream); break;
+    case kVec64x64: launch_vectors_split<F32, 4, 4, 1, 1, 1>(a, stream); break;
+    case kVec64x128: launch_vectors_split<F32, 2, 4, 2, 2, 2>(a, stream); break;
+    default: launch_vectors_cols(a, stream); break;
+  }
+  launch_vectors_norm(a, stream);
+}
+
 bool vec_d_ok(int d) { return d >= 16 && d <= 1024 && d % 16 == 0; }
 
 }  // namespace
@@ -648,6 +677,16 @@ extern "C" lilicorr_status lilicorr_candidate_vectors(const int32_t* ids, const 
       !aligned16(out_vec))
     return LILICORR_ERR_ALIGNMENT;
   const unsigned char* p = static_cast<const unsigned char*>(packed_w);
+  const int kernel = vec_kernel(M, V, d, e_dtype == LILICORR_F32);
+  if (kernel != kVecRows) {
+    const VecGeom g = vec_geom(d, M);
+    const ColsArgs a{ids, E, p, M, V, d, g.nbp, g.dkp, in_vec, out_vec};
+    if (e_dtype == LILICORR_F32)
+      launch_vectors_spread<true>(kernel, a, stream);
+    else
+      launch_vectors_spread<false>(kernel, a, stream);
+    return launch_status();
+  }
   if (e_dtype == LILICORR_BF16) {
     const VecGeom g = vec_geom(d, M);
     const int64_t rows_wg = (int64_t)g.rm * 16;

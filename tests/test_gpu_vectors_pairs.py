@@ -134,6 +134,40 @@ def test_vectors_f32_rows(lib, d, M):
         assert err <= 4 * np.sqrt(d) * 2.0 ** -24, f"d={d}: row error {err:.2e}"
 
 
+@pytest.mark.parametrize("e_dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("d,M", [(16, 1), (48, 1025), (240, 129), (256, 512),  # split tiles, 16 x 32 up
+                                 (272, 900), (512, 1023), (1008, 600), (1024, 1000),
+                                 (528, 2100), (784, 4100), (1024, 2049)])  # 128 x 128 (bf16)
+def test_vectors_spread_columns(lib, d, M, e_dtype):
+    """Columns of a row spread over workgroups, rows scaled to unit norm by a second kernel: every
+    tile of the dispatch, ragged rows and columns, half-empty last k-blocks, ids outside the table.
+    A table row of infinities sits behind every row of the d % 32 == 16 cases: a read past a row's
+    end would show. The bound is that of d fp32 additions, as above."""
+    V = 400
+    print(f"vectors spread d={d} M={M} {e_dtype}", flush=True)
+    rng = np.random.default_rng(d + M)
+    E = (rng.standard_normal((V, d)) * 0.05).astype(np.float32)
+    E[1::2] = np.inf
+    W_in = (rng.standard_normal((d, d)) / np.sqrt(d)).astype(np.float32)
+    W_out = (rng.standard_normal((d, d)) / np.sqrt(d)).astype(np.float32)
+    ids = (2 * rng.integers(0, V // 2, size=M)).astype(np.int32)
+    bad = [M - 1, M // 3] if M > 3 else []
+    ids[bad] = [V, -1][:len(bad)]
+    E = torch.from_numpy(E).to(torch.bfloat16) if e_dtype == "bf16" else torch.from_numpy(E)
+    giv, gov = _gpu_vectors(lib, ids[None, :, None], E, torch.from_numpy(W_in),
+                            torch.from_numpy(W_out))
+    giv, gov = giv.reshape(M, d), gov.reshape(M, d)
+    for r in bad:
+        assert (giv[r] == 0).all() and (gov[r] == 0).all(), f"row {r}"
+    ok = np.flatnonzero((ids >= 0) & (ids < V))
+    rows = E.double().numpy()[ids[ok]]
+    for g, W in ((giv, W_in), (gov, W_out)):
+        u = rows @ W.astype(np.float64)
+        u /= np.linalg.norm(u, axis=1, keepdims=True)
+        err = np.linalg.norm(g[ok] - u, axis=1).max()
+        assert err <= 4 * np.sqrt(d) * 2.0 ** -24, f"d={d}: row error {err:.2e}"
+
+
 def test_vectors_identity_weights(lib):
     d, V = 64, 50
     rng = np.random.default_rng(9)
