@@ -569,11 +569,32 @@ __device__ __forceinline__ void write_row(uint64_t merged, double lse, int64_t r
   }
 }
 
+// What one workgroup found in its part of a row (K best keys, exp sum S at reference C, `any` finite
+// element), by one wave: the row's outputs when it had the whole row, else a record for the merge.
+__device__ __forceinline__ void write_part(uint64_t merged, float S, int C, bool any, int64_t row,
+                                           int part, int split, int K, int32_t* ids, float* logp,
+                                           float* feat, unsigned char* partials) {
+  if (split == 1) {
+    write_row(merged, (log2((double)S) + (double)C) / (double)kLog2eF, row, K, ids, logp, feat);
+    return;
+  }
+  const int lane = lane_id();
+  unsigned char* q = partials + ((size_t)row * split + part) * partial_stride(K);
+  Partial* hdr = reinterpret_cast<Partial*>(q);
+  if (lane == 0) {
+    hdr->cref = C;
+    hdr->cvalid = any ? 1 : 0;
+    hdr->s = S;
+    hdr->pad = 0;
+  }
+  if (lane < K) reinterpret_cast<uint64_t*>(q + sizeof(Partial))[lane] = merged;
+}
+
 template <bool BF16>
 __global__ __launch_bounds__(kTopkWaves * kWave, 4) void topk_lse_kernel(
-    const void* __restrict__ logits, int64_t V, int K, int32_t* __restrict__ ids,
-    float* __restrict__ logp, float* __restrict__ feat, int wait_limit,
-    uint32_t* __restrict__ status) {
+    const void* __restrict__ logits, int64_t V, int K, int split, int32_t* __restrict__ ids,
+    float* __restrict__ logp, float* __restrict__ feat, unsigned char* __restrict__ partials,
+    int wait_limit, uint32_t* __restrict__ status) {
   constexpr int EPC = ElemTraits<BF16>::kEPC;
   constexpr int U = kPerLane / EPC;
   constexpr int TILE = U * kWave;  // chunks per wave tile
@@ -582,9 +603,12 @@ __global__ __launch_bounds__(kTopkWaves * kWave, 4) void topk_lse_kernel(
 
   const int lane = lane_id();
   const int wave = (int)uniform32(threadIdx.x / kWave);
-  const int64_t row = blockIdx.x;
+  const int64_t row = blockIdx.x / split;
+  const int part = blockIdx.x % split;
   const int64_t rowbase = row * V;
-  const int64_t g0 = rowbase, g1 = rowbase + V;
+  const int64_t span = (V + split - 1) / split;
+  const int64_t g0 = rowbase + (int64_t)part * span;
+  const int64_t g1 = rowbase + ((int64_t)(part + 1) * span < V ? (int64_t)(part + 1) * span : V);
 
   if (threadIdx.x == 0) {
     sh.T = 0;
@@ -696,7 +720,7 @@ __global__ __launch_bounds__(kTopkWaves * kWave, 4) void topk_lse_kernel(
     if (sh.cvalid[i]) S += ldexpf(sh.s[i], sh.cref[i] - C);
   const uint64_t merged = cons.L;
 
-  write_row(merged, (log2((double)S) + (double)C) / (double)kLog2eF, row, K, ids, logp, feat);
+  write_part(merged, S, C, any, row, part, split, K, ids, logp, feat, partials);
 }
 
 // ---- whole rows and long segments, no consumer wave -------------------------------------------
@@ -1059,19 +1083,7 @@ __global__ __launch_bounds__(NW* kWave) void topk_row_kernel(
     }
     if (lane >= K) merged = 0ull;
   }
-  if (split == 1) {
-    write_row(merged, (log2((double)S) + (double)C) / (double)kLog2eF, row, K, ids, logp, feat);
-  } else {
-    unsigned char* q = partials + ((size_t)row * split + part) * partial_stride(K);
-    Partial* hdr = reinterpret_cast<Partial*>(q);
-    if (lane == 0) {
-      hdr->cref = C;
-      hdr->cvalid = any ? 1 : 0;
-      hdr->s = S;
-      hdr->pad = 0;
-    }
-    if (lane < K) reinterpret_cast<uint64_t*>(q + sizeof(Partial))[lane] = merged;
-  }
+  write_part(merged, S, C, any, row, part, split, K, ids, logp, feat, partials);
 }
 
 // ---- merging a row's segments ------------------------------------------------------------------
@@ -1237,36 +1249,74 @@ __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(
 }
 
 // Which kernel takes a call, with how many waves per workgroup, and how many workgroups share a row.
-//
-// From 1024 rows on (four per compute unit) the streaming kernel takes whole rows, unless its
-// consumer's ~K (1 + ln(V / K)) records per row weigh more than what the extra wave saves: above
-// K = 16 and below V = 4000 K the row kernel does, four waves each (us, streaming / row kernel:
-// 1024 x 151936 K = 16 52.8 / 55.9, K = 32 56.7 / 62.5, K = 48 75.9 / 72.5; 2048 x 60000 K = 8
-// 45.0 / 49.8, K = 32 82.3 / 66.4; 4000 x 32000 K = 48 186 / 109).
-// Fewer rows take the row kernel: 16 waves a row while every workgroup has a compute unit of its
-// own, else eight, else (bf16, whose exp sums keep the vector units busy) four once eight would
-// need a second round (256 x 151936 K = 16: 20.5 against 30.9 with split rows in the streaming
-// kernel; 512 K = 8: 31.6 against 34.2; 700 x 60000 K = 32: 32.6 against 66.2; 800 x 151936: four
-// waves 54.1, eight 65.7, streaming 64.7; fp32 768 x 131072 K = 32: 69.9, 78.1 with four waves,
-// 87.1), and no more waves than tiles.
+// The streaming kernel pays ~K (1 + ln(V / K)) records per row in its one consumer wave, the row
+// kernel a threshold search and a sort of each wave's survivors whatever V is; so long rows with a
+// small K belong to the first, and where the line lies depends on how many rows share a compute
+// unit. Measured, us, streaming / row kernel, normal logits of standard deviation 2:
+//  * from 1024 rows on (four per compute unit) up to K = 16 always (1024 x 151936 K = 16 52.8 /
+//    55.9), above it by V against K: bf16 2048 x 60000 K = 32 82.3 / 66.4, 4000 x 32000 K = 48
+//    186 / 109, 1500 x 151936 K = 32 93.0 / 87.0; fp32 2200 x 100003 K = 48 5% for streaming.
+//    Just above 1024 rows the row kernel's fifth workgroup per compute unit runs alone, and
+//    streaming wins earlier (1040 x 100003 K = 32 51.9 / 58.2);
+//  * bf16 from 513 to 1023 rows while K is at most 32 and V at least 3500 K (640 x 151936 K = 16
+//    39.7 / 45.2, 800 x 100003 K = 8 34.0 / 38.1, 1000 x 20001 K = 2 13.8 / 16.4, but 580 x 60000
+//    K = 32 37 / 30), up to 512 rows while K is at most 8 and V at least 7000 K (512 x 60000 K = 2
+//    16.0 / 18.2, K = 16 5% for the row kernel) and V below 200000, where a row is so long that the
+//    row kernel's fixed part no longer counts (400 x 262144 K = 8 46.0 / 42.6);
+//  * fp32, whose exp sums weigh half as much against its bytes, from 513 rows at V >= 2000 K (800 x
+//    100003 K = 32 61.2 / 68.1; but 640 x 262144 K = 2 113 / 105), up to 512 with K at most 32 at
+//    4000 K (300 x 100003 K = 8 28.2 / 34.1, 400 x 262144 K = 48 86.8 / 79.5).
+// 257 to 340 rows are more than one round of whole rows but not two, and 513 to 640 more than two but
+// not three: long rows are split over four or two streaming workgroups there (300 x 262144 K = 8
+// 36.4, whole rows 44.7 / 41.6; fp32 580 x 262144 K = 48 107, whole rows 119 / 118).
+// The row kernel takes 16 waves a row while every workgroup has a compute unit of its own, else
+// eight (512 x 32000 K = 8 13.9, four 14.3, with 262144 logits K = 32 52.0 against 60), else (bf16
+// below 100000 logits) four once eight would need a second round (640 x 32000 K = 16 19.2 against
+// 22.0; at 100003 K = 48 48.7 against 46.4), and no more waves than tiles.
 // With fewer rows than compute units a row is split over workgroups of at least one tile per wave
 // (32768 logits); the merge launch costs ~5 us, so two workgroups only pay from 196608 logits
 // on (64 x 151936: four workgroups a row 16.8, one 18.6; 128 x 151936: two 20.2, one 18.8;
-// 100 x 262144: two 23.5, one 24.9; 16 x 151936 K = 8: 14.4, against 14.7 in 19 segments of one
-// 8192-logit tile each).
+// 100 x 262144: two 23.5, one 24.9). Above K = 32 the parts' longer lists cost more than they save
+// below 200000 logits (16 x 100003 K = 48 19.6 whole, 23.1 split); up to K = 8 eight-wave workgroups
+// of one tile per wave finish sooner while all run at once (fp32 16 x 100003 K = 8 13.9 against
+// 16.4, bf16 16 x 151936 K = 8 13.7 against 14.6).
 struct TopkPlan {
   int waves;  // 0: the streaming kernel
   int split;
 };
 
+bool topk_streams(int64_t rows, int64_t V, int K, bool bf16) {
+  if (rows >= 1024) return K <= 16 || V >= (int64_t)(!bf16 ? 2000 : rows < 1152 ? 3000 : 4000) * K;
+  if (rows > 512)
+    return bf16 ? K <= 32 && V >= (int64_t)3500 * K : V >= (int64_t)2000 * K && (K > 8 || V < 200000);
+  return rows > 256 && K <= (bf16 ? 8 : 32) && V >= (int64_t)(bf16 ? 7000 : 4000) * K &&
+         !(bf16 && V >= 200000);
+}
+
 TopkPlan topk_plan(int64_t rows, int64_t V, int K, bool bf16) {
-  if (rows >= 1024) return {K > 16 && V < (int64_t)4000 * K ? 4 : 0, 1};
+  if (rows > 256 && rows <= 340 && V >= (bf16 ? 150000 : 200000) && V >= (int64_t)16000 * K)
+    return {0, 4};
+  if (rows > 512 && rows <= 640 && V >= 200000 && (bf16 ? K <= 32 : K > 8)) return {0, 2};
+  if (topk_streams(rows, V, K, bf16)) return {0, 1};
+  const int64_t small = (V + 16383) / 16384;
+  if (K <= 8 && V > 65536 && rows * small <= 256) return {8, (int)small};
   int64_t split = 256 / rows;
   if (split > V / 32768) split = V / 32768;
-  if (split < 1 || (split == 2 && V < 196608)) split = 1;
-  int waves = rows * split <= 256 ? 16 : (rows <= 640 || !bf16 ? 8 : 4);
+  if (split < 1 || (split == 2 && V < 196608) || (K > 32 && V < 200000)) split = 1;
+  int waves = rows * split <= 256 ? 16 : 8;
+  if (rows >= 1024 || (rows > 512 && bf16 && V < 100000)) waves = 4;
   while (waves > 4 && (int64_t)(waves / 2) * kWave * kPerLane >= V) waves /= 2;
   return {waves, (int)split};
+}
+
+// The most workgroups that may share a row: what the size of the workspace allows for. About four per
+// compute unit, none with less than 12288 logits, or parts of 8192 where 512 workgroups hold them.
+int topk_max_parts(int64_t rows, int64_t V) {
+  const int64_t by_fill = (1024 + rows - 1) / rows, by_len = V / 12288;
+  int64_t s = by_fill < by_len ? by_fill : by_len;
+  const int64_t t = (V + 8191) / 8192;
+  if (s < by_fill && t > 1 && t <= 256 && rows * t <= 512) s = t;
+  return (int)(s < 1 ? 1 : s > 256 ? 256 : s);
 }
 
 bool topk_args_ok(int64_t N, int64_t B, int64_t V, int K) {
@@ -1282,14 +1332,16 @@ bool topk_args_ok(int64_t N, int64_t B, int64_t V, int K) {
 
 using namespace lilicorr;
 
-// workspace: the status header, then (rows split over several workgroups) the partial results
+// workspace: the status header, then (rows split over several workgroups) the partial results, for the
+// largest number of parts that a row may be given: topk_plan gives no more, for either type
+// (4 <= 1024 / rows up to 340 rows; ceil(V / 16384) <= V / 12288 and V / 8192 above 65536 logits).
 inline size_t topk_workspace_need(int64_t rows, int split, int K) {
   return kStatusBytes + (split == 1 ? 0 : (size_t)rows * split * partial_stride(K));
 }
 
 extern "C" size_t lilicorr_topk_workspace_bytes(int64_t N, int64_t B, int64_t V, int K) {
   if (!topk_args_ok(N, B, V, K) || K > 64 || K > V) return 0;
-  return topk_workspace_need(N * B, topk_plan(N * B, V, K, true).split, K);
+  return topk_workspace_need(N * B, topk_max_parts(N * B, V), K);
 }
 
 extern "C" lilicorr_status lilicorr_topk_wait_status(const void* workspace, hipStream_t stream) {
@@ -1324,7 +1376,7 @@ static lilicorr_status topk_launch(const void* logits, lilicorr_dtype dtype, int
   const int64_t rows = N * B;
   const TopkPlan plan = topk_plan(rows, V, K, bf16);
   const int split = plan.split;
-  const size_t need = topk_workspace_need(rows, split, K);
+  const size_t need = topk_workspace_need(rows, topk_max_parts(rows, V), K);
   if (!workspace || workspace_bytes < need) return LILICORR_ERR_WORKSPACE;
   if (!aligned16(workspace)) return LILICORR_ERR_ALIGNMENT;
   if (rows * split > 0x7fffffffll) return LILICORR_ERR_UNSUPPORTED;
@@ -1346,7 +1398,7 @@ static lilicorr_status topk_launch(const void* logits, lilicorr_dtype dtype, int
       row_kernel(bf, std::integral_constant<int, 4>{});
     else
       hipLaunchKernelGGL(topk_lse_kernel<decltype(bf)::value>, grid, dim3(kTopkWaves * kWave), 0,
-                         stream, logits, V, K, ids, logp, feat, g_wait_limit.load(), status);
+                         stream, logits, V, K, split, ids, logp, feat, ws, g_wait_limit.load(), status);
   };
   if (bf16)
     dispatch(std::true_type{});

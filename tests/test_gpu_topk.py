@@ -210,6 +210,13 @@ ROW_CASES = [
     (70, 98310, 2, "normal"), (1, 262147, 50, "ties"), (90, 196609, 3, "normal"),
     # eight waves (257 rows), four (641 bf16; 1024 with K above V / 4000 and 16)
     (257, 2100, 9, "normal"), (641, 700, 5, "ties"), (1024, 600, 17, "normal"),
+    # eight-wave workgroups of one tile per wave (K <= 8 above 65536 logits), rows whole above K = 32
+    (3, 65537, 8, "normal"), (31, 131075, 2, "ties"), (2, 99991, 33, "normal"),
+    # streaming: whole rows by V against K from 257 rows, four workgroups a row, and beside them the
+    # row kernel just below each line (bf16: 7000 K to 512 rows, 3500 K above; fp32: 4000 K, 2000 K)
+    (261, 28003, 4, "normal"), (513, 14003, 4, "ties"), (600, 13999, 7, "normal"),
+    (258, 200007, 2, "normal"), (513, 200003, 9, "normal"),
+    (1030, 52001, 17, "normal"),
     # every tile above the last threshold, all the best logits in one lane's groups, one value,
     # fewer finite logits than K, negative thresholds
     (2, 20011, 24, "ascending"), (2, 40000, 40, "one lane"), (2, 40001, 64, "equal"),
