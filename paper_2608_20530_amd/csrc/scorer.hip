@@ -3,7 +3,7 @@
 // stack of pre-norm bidirectional Transformer layers over each request's candidate lattice of
 // S slots x K candidates, with per-head slot-distance and same-slot attention biases.
 //
-// One layer is seven launches:
+// One layer is seven launches (few rows: the QKV and SiLU products make their own norms, five):
 //   rmsnorm -> bf16            X fp32 [M][H] -> xn bf16                       (HBM bound)
 //   GEMM  xn . Wqkv            -> Q, K bf16 [M][2H] and V^T bf16 [N][H][Lv]   (matrix cores)
 //   lattice attention          one workgroup per (request, head); K and V^T of the request in LDS
@@ -35,7 +35,6 @@ namespace lilicorr {
 namespace {
 
 constexpr int kHd = 128;  // head width
-constexpr float kEps = 1e-6f;
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kAttnThreads = 512;
 constexpr int kMaxL = 256;
@@ -511,7 +510,7 @@ extern "C" lilicorr_status lilicorr_scorer_forward(float* X, int64_t N, int64_t 
   at.S = (int)S; at.K = K; at.L = L; at.Lv = w.Lv; at.Lp = (L + 31) / 32 * 32; at.H = H;
   at.heads = heads;
   const size_t attn_lds = attn_lds_bytes(at.Lp, at.S);
-
+  const bool norm_qkv = gemm_norms(M, H, 3 * H), norm_w1 = gemm_norms(M, H, F);
 
   for (int li = 0; li < layers; ++li) {
     const unsigned char* lp = static_cast<const unsigned char*>(packed) + (size_t)li * pl.total;
@@ -524,19 +523,21 @@ extern "C" lilicorr_status lilicorr_scorer_forward(float* X, int64_t N, int64_t 
     at.dist = reinterpret_cast<const float*>(lp + pl.dist);
     at.same = reinterpret_cast<const float*>(lp + pl.same);
 
-    launch_rmsnorm(X, g_attn, xn, M, H, stream);
+    if (!norm_qkv) launch_rmsnorm(X, g_attn, xn, M, H, stream);
     GemmArgs g{};
+    g.Xn = X; g.g = g_attn;
     g.A = xn; g.B = wqkv; g.M = M; g.K = H; g.N = 3 * H; g.Y = qk; g.Vt = vt; g.H = H; g.L = L;
     g.Lv = w.Lv;
-    launch_gemm<kModeQKV>(g, stream);
+    launch_gemm<kModeQKV>(g, stream, norm_qkv);
     launch_attention(at, N, attn_lds, stream);
     GemmArgs r{};
     r.A = ao; r.B = wo; r.M = M; r.K = H; r.N = H; r.X = X;
     launch_gemm<kModeResid>(r, stream);
-    launch_rmsnorm(X, g_ffn, xn, M, H, stream);
+    if (!norm_w1) launch_rmsnorm(X, g_ffn, xn, M, H, stream);
     GemmArgs f{};
+    f.Xn = X; f.g = g_ffn;
     f.A = xn; f.B = w1; f.M = M; f.K = H; f.N = F; f.Y = hs;
-    launch_gemm<kModeSilu>(f, stream);
+    launch_gemm<kModeSilu>(f, stream, norm_w1);
     GemmArgs d{};
     d.A = hs; d.B = w2; d.M = M; d.K = F; d.N = H; d.X = X;
     launch_gemm<kModeResid>(d, stream);

@@ -28,6 +28,8 @@ typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
 constexpr uint32_t kFragBytes = 1024;  // one fragment
 constexpr int kGemmThreads = 512;      // eight waves
+constexpr int kNormMaxK = 1024;        // widest rows that a product normalises itself
+constexpr float kEps = 1e-6f;          // of RMSNorm
 constexpr int kGroup = 8;              // row blocks per tile group (L2 blocking of the grid)
 
 // fp32 -> bf16, round to nearest even: one v_cvt_pk_bf16_f32 per pair of values on gfx950
@@ -61,6 +63,8 @@ struct GemmArgs {
   uint16_t* Y;         // silu: bf16(silu(A . B)) in fragment order; qkv: Q and K, Y[M][2H]
   uint16_t* Vt;        // qkv: V columns transposed per request, Vt[M / L][H][Lv]
   int H, L, Lv;
+  const float* Xn;     // where the kernel normalises its own rows: A = rms norm of Xn[M][K] ...
+  const float* g;      // ... times g[K], rounded to bf16
 };
 
 // One accumulator tile of the products (weights x activations): lane holds columns
@@ -366,7 +370,11 @@ void gemm_big_kernel(GemmArgs p) {
 // of a few hundred KB through each compute unit and how many compute units have any work, so the
 // contraction is cut rather than left to few workgroups (M = 120, H = 1024, F = 2048: 6.2, 3.3,
 // 5.0 and 5 us for the four products against 21, 18, 18.5 and 26 us from 128 x 256 tiles).
-template <int MODE, int TM, int TN, int WM, int WN, int RING>
+//
+// NORM (QKV and SiLU products of few rows, gemm_norms): the workgroup makes its own A rows,
+// the bf16 rounding of their RMSNorm (the same operations in the same order as
+// rmsnorm_bf16_kernel), in LDS while its first weights are on their way, and reads A from there.
+template <int MODE, bool NORM, int TM, int TN, int WM, int WN, int RING>
 __global__ __launch_bounds__(kGemmThreads) __attribute__((amdgpu_waves_per_eu(2, 2)))
 void gemm_split_kernel(GemmArgs p) {
   constexpr int KS = 8 / (WM * WN), BM = 16 * TM * WM, BN = 16 * TN * WN;
@@ -392,16 +400,35 @@ void gemm_split_kernel(GemmArgs p) {
   for (int i = 0; i < TM; ++i)
     offA[i] = a0 + i < row_blocks ? (a0 + i) * kFragBytes + voff : kOut;
 
+  // NORM: this wave's rows wave, wave + 8, .. of the tile, 256 columns a step, all in flight
+  constexpr int NR = BM / 8, NV = kNormMaxK / 256;
+  f32x4 x[NORM ? NR : 1][NV], gv[NV];
+  if constexpr (NORM) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      int64_t row = tm * BM + wave + r * 8;
+      row = row < p.M ? row : p.M - 1;  // such rows reach no output that is stored
+#pragma unroll
+      for (int j = 0; j < NV; ++j)
+        x[r][j] = j * 256 < p.K ? *reinterpret_cast<const f32x4*>(p.Xn + row * p.K + (j * 64 + lane) * 4)
+                                : f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+#pragma unroll
+    for (int j = 0; j < NV; ++j)
+      gv[j] = j * 256 < p.K ? *reinterpret_cast<const f32x4*>(p.g + (j * 64 + lane) * 4)
+                            : f32x4{0.f, 0.f, 0.f, 0.f};
+  }
   bf16x8 a[RING][TM], b[RING][TN];
   auto load = [&](int r, int step) {
     const int kb = ks + step * KS;
     // uniform; steps past the end multiply zeros
     const uint32_t past = kb < KB ? 0u : kOut;
     const uint32_t k = kb < KB ? (uint32_t)kb : 0u;
+    if constexpr (!NORM)
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
-      a[r][i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
-                                               ra, offA[i] | past, (int)(k * stepA), 0));
+      for (int i = 0; i < TM; ++i)
+        a[r][i] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(
+                                                 ra, offA[i] | past, (int)(k * stepA), 0));
 #pragma unroll
     for (int j = 0; j < TN; ++j)
       b[r][j] = __builtin_bit_cast(
@@ -419,9 +446,44 @@ void gemm_split_kernel(GemmArgs p) {
 #pragma unroll
   for (int r = 0; r < RING; ++r) load(r, r);
   __builtin_amdgcn_sched_barrier(0);
+  // A in LDS: fragment (kb, row block) as everywhere, its 16-byte piece (row r, quarter q) at
+  // q * 16 + (r ^ (4 kb + q) % 16), so that the pieces that one row's write covers lie in distinct
+  // banks
+  if constexpr (NORM) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      float ss = 0.f;
+#pragma unroll
+      for (int j = 0; j < NV; ++j)
+        ss += x[r][j][0] * x[r][j][0] + x[r][j][1] * x[r][j][1] + x[r][j][2] * x[r][j][2] +
+              x[r][j][3] * x[r][j][3];
+      ss = wave_sum(ss);
+      const float inv = 1.0f / sqrtf(ss / (float)p.K + kEps);
+      const int rl = wave + r * 8;
+#pragma unroll
+      for (int j = 0; j < NV; ++j) {
+        const int col = (j * 64 + lane) * 4, kb = col >> 5, q = (col >> 3) & 3;
+        if (col < p.K)
+          *reinterpret_cast<u32x2*>(split_smem + (uint32_t)(kb * (TM * WM) + (rl >> 4)) * kFragBytes +
+                                    (q * 16 + ((rl & 15) ^ ((kb * 4 + q) & 15))) * 16 + (col & 4) * 2) =
+              u32x2{pack_bf16x2(x[r][j][0] * inv * gv[j][0], x[r][j][1] * inv * gv[j][1]),
+                    pack_bf16x2(x[r][j][2] * inv * gv[j][2], x[r][j][3] * inv * gv[j][3])};
+      }
+    }
+    __syncthreads();
+  }
   for (int s = 0; s < nsteps; s += RING) {
 #pragma unroll
     for (int r = 0; r < RING; ++r) {
+      if constexpr (NORM) {
+        const int kb = ks + (s + r) * KS, q = lane >> 4;  // zeros past the end
+        const uint32_t at = (uint32_t)(q * 16 + ((lane & 15) ^ ((kb * 4 + q) & 15))) * 16u;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          a[r][i] = kb < KB ? *reinterpret_cast<const bf16x8*>(
+                                  split_smem + (uint32_t)(kb * (TM * WM) + wm * TM + i) * kFragBytes + at)
+                            : bf16x8{};
+      }
 #pragma unroll
       for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -433,6 +495,7 @@ void gemm_split_kernel(GemmArgs p) {
     }
   }
 
+  if constexpr (NORM) __syncthreads();  // the partial sums take the place of A
   constexpr int F = TM * TN;
   f32x4* mine = part + (size_t)(ks * WM * WN + blk) * F * 64 + lane;
 #pragma unroll
@@ -467,16 +530,17 @@ void launch_gemm_big(const GemmArgs& a, hipStream_t stream) {
                      stream, a);
 }
 
-template <int MODE, int TM, int TN, int WM, int WN, int RING>
+template <int MODE, bool NORM, int TM, int TN, int WM, int WN, int RING>
 void launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
   constexpr int BM = 16 * TM * WM, BN = 16 * TN * WN;
-  constexpr size_t lds = (size_t)8 * TM * TN * 64 * 16;
+  constexpr size_t part = (size_t)8 * TM * TN * 64 * 16, rows = NORM ? (size_t)BM * kNormMaxK * 2 : 0;
+  constexpr size_t lds = part > rows ? part : rows;
   static const hipError_t attr = hipFuncSetAttribute(
-      reinterpret_cast<const void*>(gemm_split_kernel<MODE, TM, TN, WM, WN, RING>),
+      reinterpret_cast<const void*>(gemm_split_kernel<MODE, NORM, TM, TN, WM, WN, RING>),
       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
   (void)attr;
   const int64_t tiles = (a.M + BM - 1) / BM * (a.N / BN);
-  hipLaunchKernelGGL((gemm_split_kernel<MODE, TM, TN, WM, WN, RING>), dim3((unsigned)tiles),
+  hipLaunchKernelGGL((gemm_split_kernel<MODE, NORM, TM, TN, WM, WN, RING>), dim3((unsigned)tiles),
                      dim3(kGemmThreads), lds, stream, a);
 }
 
@@ -490,21 +554,33 @@ void launch_gemm_split(const GemmArgs& a, hipStream_t stream) {
 //   M = 3840, K = 1024, N = 1024: 128 x 128 17.9, 64 x 128 (two rounds) 19.9, big 22.7
 constexpr int64_t kOneRound = 256;
 
+// Whether a product makes its own normalised rows: a launch of rmsnorm_bf16_kernel (3 us, little of
+// it work) fewer, for each workgroup's read of its rows in fp32 and their norm ahead of its first
+// product. That pays with 16 x 32 tiles (two-layer forwards, us: 12 rows at H = 1024 52.6 -> 48.8, 48
+// at 768 51.4 -> 46.8); 32-row tiles read twice as much before they start (120 rows at 1024 67.2 without, 69.4
+// with).
+inline bool gemm_norms(int64_t M, int K, int N) {
+  return K <= kNormMaxK && (M + 15) / 16 * (N / 32) <= kOneRound;
+}
+
+// norm: A is the RMSNorm of a.Xn (gemm_norms holds), else a.A.
 template <int MODE>
-void launch_gemm(const GemmArgs& a, hipStream_t stream) {
+void launch_gemm(const GemmArgs& a, hipStream_t stream, bool norm = false) {
   auto fits = [&](int bm, int bn) { return (a.M + bm - 1) / bm * (a.N / bn) <= kOneRound; };
+  if constexpr (MODE != kModeResid)
+    if (norm) return launch_gemm_split<MODE, true, 1, 2, 1, 1, 4>(a, stream);
   if (fits(16, 32))
-    launch_gemm_split<MODE, 1, 2, 1, 1, 4>(a, stream);
+    launch_gemm_split<MODE, false, 1, 2, 1, 1, 4>(a, stream);
   else if (fits(32, 32))
-    launch_gemm_split<MODE, 2, 2, 1, 1, 4>(a, stream);
+    launch_gemm_split<MODE, false, 2, 2, 1, 1, 4>(a, stream);
   else if (fits(32, 64))
-    launch_gemm_split<MODE, 2, 4, 1, 1, 4>(a, stream);
+    launch_gemm_split<MODE, false, 2, 4, 1, 1, 4>(a, stream);
   else if (fits(64, 64))
-    launch_gemm_split<MODE, 4, 4, 1, 1, 3>(a, stream);
+    launch_gemm_split<MODE, false, 4, 4, 1, 1, 3>(a, stream);
   else if (fits(64, 128))
-    launch_gemm_split<MODE, 4, 4, 1, 2, 3>(a, stream);
+    launch_gemm_split<MODE, false, 4, 4, 1, 2, 3>(a, stream);
   else if (fits(128, 128))
-    launch_gemm_split<MODE, 4, 4, 2, 2, 3>(a, stream);
+    launch_gemm_split<MODE, false, 4, 4, 2, 2, 3>(a, stream);
   else
     launch_gemm_big<MODE>(a, stream);
 }

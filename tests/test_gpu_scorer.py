@@ -93,6 +93,10 @@ TILE_CASES = [
     (workloads.ScorerConfig(N=3, S=9, K=13, H=768, heads=6, F=1152), "full"),  # 351: odd lattice
     (workloads.ScorerConfig(N=11, S=9, K=13, H=768, heads=6, F=1152), "attn"),  # 1287: 128x128, 64x64
     (workloads.ScorerConfig(N=11, S=9, K=13, H=768, heads=6, F=1152), "ffn"),   # 64x128, 64x64
+    # 16 x 32 tiles: the QKV and SiLU products make their own norms up to H = 1024, and not above
+    (workloads.ScorerConfig(N=1, S=4, K=3), "full"),
+    (workloads.ScorerConfig(N=2, S=4, K=5, H=768, heads=6, F=1152), "ffn"),
+    (workloads.ScorerConfig(N=1, S=2, K=3, H=1280, heads=10, F=256), "full"),
     # 128 x 256 tiles with a ragged last row tile: V^T value by value (L odd) and in quads
     # (L % 8 == 4), and an output width that ends in half a tile (F = 17 * 128)
     (workloads.ScorerConfig(N=17, S=9, K=13, F=2176), "attn"),
