@@ -604,7 +604,9 @@ void launch_vectors_f32(const int32_t* ids, const float* E, const unsigned char*
 // while the tiles of vectors_split_kernel fit one round of compute units the smallest such tile is
 // taken (us, bf16, with the norm pass: 128 rows 6.1, 6.5 and 8.9; 512 rows at d = 512 9.6, at 1024
 // 17.2; 4096 rows at 256 16.4 against 18.3), for fp32 from d = 256 on, there up to 512 rows (1024
-// rows at 256: 11 against 9.9). Above d = 768 the 1024-thread whole-row workgroups lose to 128 x 128
+// rows at 256: 11 against 9.9). The second launch is not worth it where the weights are a few kilobytes
+// (32 rows at d = 64 10.6 against 9.6), nor are 64 x 128 tiles that hold whole rows anyway (8192 rows at
+// d = 128 15.5 against 14.7). Above d = 768 the 1024-thread whole-row workgroups lose to 128 x 128
 // tiles at any row count (d = 1024, 2048 rows 37 against 63, 4096 64 against 72, 16384 236 against
 // 269); between 512 and 768 only while one round holds the tiles (4096 rows at 768: 48 against 41).
 enum { kVecRows = 0, kVec16x32, kVec32x32, kVec32x64, kVec64x64, kVec64x128, kVecTiles };
@@ -612,12 +614,13 @@ enum { kVecRows = 0, kVec16x32, kVec32x32, kVec32x64, kVec64x64, kVec64x128, kVe
 int vec_kernel(int64_t M, int64_t V, int d, bool f32) {
   if (V * d * (f32 ? 4 : 2) >= ((int64_t)1 << 31) || M >= ((int64_t)1 << 31)) return kVecRows;
   auto fits = [&](int bm, int bn) { return (M + bm - 1) / bm * ((d + bn - 1) / bn) * 2 <= 256; };
+  if (d <= 64 && M <= 64) return kVecRows;
   if (!f32 || d > 256 || (d == 256 && M <= 512)) {
     if (fits(16, 32)) return kVec16x32;
     if (fits(32, 32)) return kVec32x32;
     if (fits(32, 64)) return kVec32x64;
     if (fits(64, 64)) return kVec64x64;
-    if (fits(64, 128)) return kVec64x128;
+    if (d > 128 && fits(64, 128)) return kVec64x128;
   }
   if (!f32 && (d > 768 || (d > 512 && fits(128, 128)))) return kVecTiles;
   return kVecRows;

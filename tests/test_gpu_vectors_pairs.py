@@ -135,7 +135,8 @@ def test_vectors_f32_rows(lib, d, M):
 
 
 @pytest.mark.parametrize("e_dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("d,M", [(16, 1), (48, 1025), (240, 129), (256, 512),  # split tiles, 16 x 32 up
+@pytest.mark.parametrize("d,M", [(16, 1), (64, 64), (128, 4097),  # whole rows beside the spread ones
+                                 (64, 65), (48, 1025), (240, 129), (256, 512),  # split tiles, 16 x 32 up
                                  (272, 900), (512, 1023), (1008, 600), (1024, 1000),
                                  (528, 2100), (784, 4100), (1024, 2049)])  # 128 x 128 (bf16)
 def test_vectors_spread_columns(lib, d, M, e_dtype):
