@@ -869,7 +869,8 @@ __device__ __forceinline__ void row_tile(RowWave& w, Producer& pr, RowShared<NW>
 #pragma unroll
       for (int u = h * U / 2 + 1; u < (h + 1) * U / 2; ++u) m = __builtin_elementwise_max(m, cm2[u]);
       hm[h] = m[0] > m[1] ? (int)m[0] : (int)m[1];
-      const uint32_t o = hm[h] > 0 ? 0x80000000u | ((uint32_t)hm[h] << 16) : 0u;
+      // (a NaN pattern is above infinity's and bounds nothing)
+      const uint32_t o = hm[h] > 0 && hm[h] <= 0x7f80 ? 0x80000000u | ((uint32_t)hm[h] << 16) : 0u;
       w.top[h] = o > w.top[h] ? o : w.top[h];
     }
     if (__ballot((hm[0] > hm[1] ? hm[0] : hm[1]) >= tbe)) {
@@ -892,7 +893,7 @@ __device__ __forceinline__ void row_tile(RowWave& w, Producer& pr, RowShared<NW>
       hm[h] = cm[h * U / 2];
 #pragma unroll
       for (int u = h * U / 2 + 1; u < (h + 1) * U / 2; ++u) hm[h] = fmaxf(hm[h], cm[u]);
-      const uint32_t o = order_bits(hm[h]);
+      const uint32_t o = hm[h] == hm[h] ? order_bits(hm[h]) : 0u;  // NaN: a half of NaNs only
       w.top[h] = o > w.top[h] ? o : w.top[h];
     }
     if (raise) {

@@ -257,6 +257,29 @@ def test_topk_row_kernel(lib, rows, V, K, kind, bf16):
     assert np.array_equal(a[1].view(np.int32), b[1].view(np.int32))
 
 
+@pytest.mark.parametrize("bf16", [True, False], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("nan", ["every chunk", "whole tiles"])
+@pytest.mark.parametrize("rows,V,K", [
+    (2, 40000, 16), (3, 151936, 8),        # few rows, whole and in parts
+    (260, 100000, 16), (1100, 50000, 17),  # waves of more than four tiles: maxima of every form
+    (1100, 9000, 4)])                      # streaming
+def test_topk_nan_logits(lib, rows, V, K, nan, bf16):
+    """NaN logits are never candidates: the ids are those of the row with its NaNs at -inf, in every
+    kernel and wherever the NaNs stand."""
+    print(f"topk nan rows={rows} V={V} K={K} {nan} bf16={bf16}", flush=True)
+    x = _row_logits(rows, V, "normal").to(torch.bfloat16 if bf16 else torch.float32)
+    clean = x.clone()
+    at = slice(None, None, 4) if nan == "every chunk" else slice(V // 2)
+    clean[..., at] = -np.inf
+    # set by bit pattern: a converted NaN may carry a sign, and positive ones sort above infinity
+    x.view(torch.int16 if bf16 else torch.int32)[..., at] = 0x7FC0 if bf16 else 0x7FC00000
+    gi, _ = _run(lib, x, K)
+    clean = to_np(clean)[0]
+    for r in range(0, rows, max(1, rows // 12)):
+        ri, _ = oracle.topk(clean[r][None, None], K)
+        assert_equal(gi[0, r], ri[0, 0], f"ids row {r}")
+
+
 # ---- bounded waits: expiry is reported, never silent ---------------------------------------------
 
 def test_topk_wait_expiry_is_reported(lib):
