@@ -231,9 +231,13 @@ void gemm_big_kernel(GemmArgs p) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
 
+  // in this order, which the first wait's count relies on: the copies of stage 0, then the 20 loads
+  // of the later stages' copies and the first weights
   dma(0);
+  __builtin_amdgcn_sched_barrier(0);
   dma(1);
   dma(2);
+  __builtin_amdgcn_sched_barrier(0);
   load_b(b[0], 0);
   load_b(b[1], 1);
   load_b(b[2], 2);

@@ -220,8 +220,12 @@ void vectors_cols_kernel(ColsArgs p, int ntn) {
   for (int i = 0; i < 4; ++i)
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // in this order, which the first wait's count relies on: the copies of stage 0, then the 16 loads
+  // of stage 1's copies and the first weights
   dma(0);
+  __builtin_amdgcn_sched_barrier(0);
   dma(1);
+  __builtin_amdgcn_sched_barrier(0);
   load_b(b[0], 0);
   __builtin_amdgcn_sched_barrier(0);
   for (int s = 0; s < ns; ++s) {
