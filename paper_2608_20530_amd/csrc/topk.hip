@@ -1066,16 +1066,34 @@ __global__ __launch_bounds__(NW* kWave) void topk_row_kernel(
 
   uint64_t merged;
   const int total = sh.count;
-  if (total <= kWave) {
-    // rank = number of larger keys (keys are distinct)
-    const uint64_t mine = lane < total ? sh.flat[lane] : 0ull;
-    int rank = 0;
-    for (int j = 0; j < total; ++j) rank += sh.flat[j] > mine ? 1 : 0;
+  // rank = number of larger keys (keys are distinct); a lane ranks PER of them
+  auto rank_all = [&](auto per) {
+    constexpr int PER = decltype(per)::value;
+    uint64_t mine[PER];
+    int rank[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+      mine[q] = lane + q * kWave < total ? sh.flat[lane + q * kWave] : 0ull;
+      rank[q] = 0;
+    }
+    for (int j = 0; j < total; ++j) {
+      const uint64_t key = sh.flat[j];
+#pragma unroll
+      for (int q = 0; q < PER; ++q) rank[q] += key > mine[q] ? 1 : 0;
+    }
     sh.out[lane] = 0ull;
     wave_lds_fence();
-    if (lane < total && rank < K) sh.out[rank] = mine;
+#pragma unroll
+    for (int q = 0; q < PER; ++q)
+      if (lane + q * kWave < total && rank[q] < K) sh.out[rank[q]] = mine[q];
     wave_lds_fence();
     merged = lane < K ? sh.out[lane] : 0ull;
+  };
+  if (total <= kWave) {
+    rank_all(std::integral_constant<int, 1>{});
+  } else if (total <= 2 * kWave) {
+    // (usual from K = 48 on; 64 rows of 10000 fp32 logits, K = 48: 17.5 us, by sorting 18.5)
+    rank_all(std::integral_constant<int, 2>{});
   } else {
     merged = 0ull;
     for (int b = 0; b < total; b += kWave) {
@@ -1105,11 +1123,12 @@ __device__ __forceinline__ int wave_prefix_small(int c) {
 //  * when the row holds at most kMergeFast entries (split K), every entry is loaded at once
 //    (eight per thread). Partial p* whose K-th key is the largest, T, holds K keys >= T, so the
 //    row's K largest keys all reach T: only entries >= T are candidates (usually little more
-//    than K; when no partial is full, T = 0 and every key is one), compacted into LDS. Wave 0
-//    ranks them (a key's rank is the number of larger candidates; keys are distinct) and places
-//    the K largest in order; more than 64 candidates take a sort-and-merge loop;
+//    than K; when no partial is full, T = 0 and every key is one), compacted into LDS. Up to 128
+//    of them are ranked by wave 0 (a key's rank is the number of larger candidates; keys are
+//    distinct), which places the K largest in order;
 //  * otherwise wave w merges the lists of partials w, w + 4, ..., eight lists' loads in flight
-//    at a time, and wave 0 merges the four results through LDS.
+//    at a time, and wave 0 merges the four results through LDS (sorting the candidates 64 at a time
+//    took 38.6 us for the whole call at one row of 600000 fp32 logits in 18 parts, K = 48; 25.1 now).
 constexpr int kMergeThreads = 256;
 constexpr int kMergeBatch = 8;
 constexpr int kMergeFast = kMergeThreads * kMergeBatch;
@@ -1192,28 +1211,29 @@ __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(
     for (int i = 0; i < kMergeBatch; ++i)
       if (tid + kMergeThreads * i < E && kv[i] != 0ull && kv[i] >= T) sCand[off++] = kv[i];
     __syncthreads();
-    if (wave != 0) return;
     const int total = sCount;
-    if (total <= kWave) {
-      const uint64_t mine = lane < total ? sCand[lane] : 0ull;
-      int rank = 0;
-      for (int i = 0; i < total; ++i) rank += sCand[i] > mine ? 1 : 0;
-      if (lane < total && rank < K) sL[0][rank] = mine;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      merged = lane < K ? sL[0][lane] : 0ull;
-    } else {
-      for (int b = 0; b < total; b += kWave) {
-        const uint64_t v = b + lane < total ? sCand[b + lane] : 0ull;
-        merged = b == 0 ? sort_desc64_u64(v) : merge_desc64(merged, sort_desc64_u64(v));
-      }
-    }
-    float S = sS[0];
+    if (total <= 2 * kWave) {
+      if (wave != 0) return;
+      uint64_t mine[2];
+      int rank[2] = {0, 0};
 #pragma unroll
-    for (int w = 1; w < NW; ++w) S += sS[w];
-    write_row(merged, (log2((double)S) + (double)C) / (double)kLog2eF, row, K, ids, logp, feat);
-    return;
+      for (int q = 0; q < 2; ++q) mine[q] = lane + q * kWave < total ? sCand[lane + q * kWave] : 0ull;
+      for (int i = 0; i < total; ++i) {
+        const uint64_t key = sCand[i];
+#pragma unroll
+        for (int q = 0; q < 2; ++q) rank[q] += key > mine[q] ? 1 : 0;
+      }
+#pragma unroll
+      for (int q = 0; q < 2; ++q)
+        if (lane + q * kWave < total && rank[q] < K) sL[0][rank[q]] = mine[q];
+      wave_lds_fence();
+      merged = lane < K ? sL[0][lane] : 0ull;
+      float S = sS[0];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) S += sS[w];
+      write_row(merged, (log2((double)S) + (double)C) / (double)kLog2eF, row, K, ids, logp, feat);
+      return;
+    }
   }
 
   bool first = true;

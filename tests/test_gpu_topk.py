@@ -257,6 +257,42 @@ def test_topk_row_kernel(lib, rows, V, K, kind, bf16):
     assert np.array_equal(a[1].view(np.int32), b[1].view(np.int32))
 
 
+# ---- rows in parts: the merge kernel's paths -------------------------------------------------------
+
+SPLIT_CASES = [
+    # row kernel in parts: a part with no finite logit, more candidates than one wave ranks, and more
+    # than 2048 partial keys
+    (3, 98310, 12, "maskblock"), (2, 300000, 64, "63 a part"), (1, 1200000, 64, "normal"),
+    (1, 1200000, 64, "maskblock"),
+    # more than 64 and more than 128 survivors to rank
+    (5, 10000, 52, "normal"), (5, 10000, 64, "ties"),
+]
+
+
+def _split_logits(rows, V, K, kind):
+    if kind == "maskblock":
+        x = _row_logits(rows, V, "normal")
+        x[..., : 2 * V // 3] = -np.inf
+        x[..., -1] = 3.0
+        return x
+    if kind == "zeros":
+        return torch.from_numpy(_edge_logits(1, rows, V, "zeros", K))
+    x = _row_logits(rows, V, "normal" if kind == "63 a part" else kind)
+    if kind == "63 a part":  # of the nine parts: no part's 64th key is above another's 63
+        for p in range(9):
+            x[..., p * ((V + 8) // 9):][..., :63] += 40
+    return x
+
+
+@pytest.mark.parametrize("bf16", [True, False], ids=["bf16", "fp32"])
+@pytest.mark.parametrize("rows,V,K,kind", SPLIT_CASES)
+def test_topk_plan_paths(lib, rows, V, K, kind, bf16):
+    print(f"plan paths rows={rows} V={V} K={K} {kind} bf16={bf16}", flush=True)
+    x = _split_logits(rows, V, K, kind)
+    x = x.to(torch.bfloat16) if bf16 else x
+    _check_rows(lib, x, K, range(0, rows, max(1, rows // 8)), f"{kind} rows={rows} V={V} K={K}")
+
+
 @pytest.mark.parametrize("bf16", [True, False], ids=["bf16", "fp32"])
 @pytest.mark.parametrize("nan", ["every chunk", "whole tiles"])
 @pytest.mark.parametrize("rows,V,K", [
