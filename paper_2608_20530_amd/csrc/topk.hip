@@ -2,8 +2,8 @@
 // (Sec. 3.2 candidate pool; implementation appendix, "Serving": normalisation and candidate
 // extraction in one kernel).
 //
-// Many rows take topk_lse_kernel, fewer (or a K large against V) topk_row_kernel, whose notes stand
-// beside it; topk_plan has the rule. topk_lse_kernel (gfx950), one workgroup per row, four waves:
+// Many rows and short ones take topk_lse_kernel, fewer (or a K large against V) topk_row_kernel, a few
+// long ones topk_small_kernel, whose notes stand beside them; topk_plan has the rule. topk_lse_kernel (gfx950), one workgroup per row, four waves:
 //  * Three producer waves stream the logits from HBM exactly once with 16-byte non-temporal
 //    buffer loads, in interleaved tiles of 64 lanes x 32 elements (4 KB of bf16); each wave
 //    issues its next tile's loads before it processes the current one.
@@ -1105,7 +1105,31 @@ __global__ __launch_bounds__(NW* kWave) void topk_row_kernel(
   write_part(merged, S, C, any, row, part, split, K, ids, logp, feat, partials);
 }
 
-// ---- merging a row's segments ------------------------------------------------------------------
+// ---- short row segments --------------------------------------------------------------------
+// A few long rows cut into segments of at most kSmallSpan logits, all running at once. What such a
+// segment waits for is one round trip to memory and then a chain of dependent steps, so every thread
+// holds its 32 logits (element tid + 256 j) from the start, all loaded before the first is used, and
+// nothing is staged, raised or flushed on the way (16 fp32 rows of 65537, K = 8: 12.8 us with the
+// merge, the row kernel 14.2 in its best split). The workgroup reduces the maximum and the exp sum
+// relative to the same integer log2 reference as the streaming kernel and writes the same partial
+// record for the merge kernel.
+// Top-K: a threshold T that at least K of the segment's elements reach, so that its K largest
+// keys all do. At K <= 8 each wave finds the K-th largest of its 64 lane maxima by a bitwise
+// search over their order bits (one ballot per bit) and T is the largest of the four; at larger K
+// (where that leaves more than 64 candidates on random logits) T is the K-th largest of all 256
+// lane maxima (every wave reads them from LDS; four ballots per bit). The elements >= T are the
+// candidates: each lane counts its own, a prefix sum over the wave places them in LDS, and wave 0
+// ranks them (a key's rank is the number of larger candidates; keys are distinct) and writes the
+// K largest in order. When more than 64 elements reach T (exact ties at T, such as a segment that
+// is all -inf), T becomes the workgroup-wide value completed over the ids of the lane maxima (the
+// smallest id holding each) where more lanes than needed hold it, which bounds the candidates by
+// key; more than 64 still take a sort-and-merge loop.
+constexpr int kSmallThreads = 256;
+constexpr int kSmallPer = 32;
+constexpr int64_t kSmallSpan = (int64_t)kSmallThreads * kSmallPer;
+constexpr int64_t kSmallFill = 512;  // workgroups that run at once (two per compute unit)
+constexpr int kSmallWaveK = 8;   // largest K whose first threshold is taken per wave
+
 // Exclusive prefix sum over the wave of a per-lane count below 64, from one ballot per bit.
 __device__ __forceinline__ int wave_prefix_small(int c) {
   int p = 0;
@@ -1118,6 +1142,192 @@ __device__ __forceinline__ int wave_prefix_small(int c) {
   return p;
 }
 
+// The largest t with at least `need` lanes of the wave holding v >= t.
+__device__ __forceinline__ uint32_t wave_kth_bits(uint32_t v, int need) {
+  uint32_t t = 0;
+#pragma unroll
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t c = t | (1u << bit);
+    if (__popcll(__ballot(v >= c)) >= need) t = c;
+  }
+  return t;
+}
+
+// The largest t such that at least `need` of the workgroup's 256 values v[] (four per lane of
+// every wave, read from LDS, so every wave finds the same t) with on[] set are >= t.
+__device__ __forceinline__ uint32_t block_kth_bits(const uint32_t (&v)[4], const bool (&on)[4],
+                                                   int need) {
+  uint32_t t = 0;
+#pragma unroll
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t c = t | (1u << bit);
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) n += __popcll(__ballot(on[i] & (v[i] >= c)));
+    if (n >= need) t = c;
+  }
+  return t;
+}
+
+template <bool BF16>
+__global__ __launch_bounds__(kSmallThreads) void topk_small_kernel(
+    const void* __restrict__ logits, int64_t V, int K, int split,
+    unsigned char* __restrict__ partials) {
+  constexpr int NW = kSmallThreads / kWave;
+  __shared__ uint64_t sCand[kSmallSpan];
+  __shared__ float sMax[NW], sSum[NW];
+  __shared__ uint32_t sKhi[kSmallThreads], sKlo[kSmallThreads];
+  __shared__ int sCount[2];
+  const int tid = threadIdx.x, lane = lane_id(), wave = tid / kWave;
+  const int64_t row = blockIdx.x / split;
+  const int part = blockIdx.x % split;
+  const int64_t span = (V + split - 1) / split;
+  const int64_t lo = (int64_t)part * span;
+  const int64_t hi = lo + span < V ? lo + span : V;
+  const int len = (int)(hi > lo ? hi - lo : 0);
+  const int64_t base = row * V + lo;
+  const int rem = len - tid;  // element j of this thread lies in the segment iff 256 j < rem
+  if (tid == 0) sCount[0] = sCount[1] = 0;
+
+  // positions past the segment load the row's first element (in bounds for any segment, even an
+  // empty one) and are masked afterwards, so no load waits behind another
+  float x[kSmallPer];
+  const int64_t rowstart = row * V;
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) {
+    const int64_t g = kSmallThreads * j < rem ? base + tid + kSmallThreads * j : rowstart;
+    if constexpr (BF16)
+      x[j] = __uint_as_float((uint32_t)static_cast<const uint16_t*>(logits)[g] << 16);
+    else
+      x[j] = static_cast<const float*>(logits)[g];
+  }
+  float m = -__builtin_inff();
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) {
+    x[j] = kSmallThreads * j < rem ? x[j] : -__builtin_inff();
+    m = fmaxf(m, x[j]);
+  }
+  const uint32_t khi = rem > 0 ? order_bits(m) : 0u;  // the lane's largest value (0: none)
+  // the threshold: at K <= 8 the largest of the waves' K-th lane maxima (about 4K candidates),
+  // else the K-th largest of all 256 lane maxima (a tighter bound for a costlier search)
+  const bool per_wave = K <= kSmallWaveK;
+  sKhi[tid] = khi;
+  const uint32_t thi = per_wave ? wave_kth_bits(khi, K) : 0u;
+  const float mw = wave_max(m);
+  if (lane == 0) {
+    sMax[wave] = mw;
+    sKlo[wave] = thi;  // the waves' thresholds (sKlo is reused for lane ids only later)
+  }
+  __syncthreads();
+  float M = sMax[0];
+  uint32_t Thi = sKlo[0];
+#pragma unroll
+  for (int w = 1; w < NW; ++w) {
+    M = fmaxf(M, sMax[w]);
+    Thi = sKlo[w] > Thi ? sKlo[w] : Thi;
+  }
+  uint32_t all_hi[4];
+  const bool every[4] = {true, true, true, true};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) all_hi[i] = sKhi[lane + kWave * i];
+  if (!per_wave) Thi = block_kth_bits(all_hi, every, K);
+  const bool valid = M > -__builtin_inff();
+  const int C = valid ? ref_for(M) : 0;
+  const float c = -(float)C;
+  float e = 0.f;
+#pragma unroll
+  for (int j = 0; j < kSmallPer; ++j) e += __builtin_amdgcn_exp2f(fmaf(x[j], kLog2eF, c));
+  e = wave_sum(e);
+  if (lane == 0) sSum[wave] = e;
+
+  // candidates (value, id) >= (Tv, Tlo): value > Tv, or value == Tv and id part >= Tlo (the first
+  // pass takes every id: value >= Tv). The order bits of -0 and +0 are equal, as are the values;
+  // Thi = 0 (fewer than K lanes holding elements, in every wave or in the workgroup, as searched)
+  // makes every element a candidate; the padding (-inf) is told apart by position when Tv is
+  // -inf. Predicates use non-short-circuit operators
+  // so that they compile to mask arithmetic rather than branches.
+  auto place = [&](auto by_id, float Tv, uint32_t Tlo, int slot) {
+    const int lim = Tv == -__builtin_inff() ? rem : kSmallThreads * kSmallPer;
+    auto cand = [&](int j) {
+      const bool in = kSmallThreads * j < lim;
+      if constexpr (decltype(by_id)::value) {
+        const uint32_t idc = 0xFFFFFFFFu - (uint32_t)(lo + tid + kSmallThreads * j);
+        return in & ((x[j] > Tv) | ((x[j] == Tv) & (idc >= Tlo)));
+      } else {
+        return in & (x[j] >= Tv);
+      }
+    };
+    int cnt = 0;
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) cnt += cand(j) ? 1 : 0;
+    int off = wave_prefix_small(cnt);
+    const int wtotal = __shfl(off + cnt, kWave - 1, kWave);
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&sCount[slot], wtotal);
+    off += __shfl(at, 0, kWave);
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j)
+      if (cand(j)) sCand[off++] = make_key(x[j], (uint32_t)(lo + tid + kSmallThreads * j));
+  };
+  place(std::false_type{}, Thi ? order_value(Thi) : -__builtin_inff(), 0u, 0);
+  __syncthreads();
+  int total = sCount[0];
+  if (total > kWave) {
+    // the K-th largest of all 256 lane maxima, then, among the lanes holding exactly that value,
+    // the id bits of their keys (the smallest id holding the lane maximum)
+    if (per_wave) Thi = block_kth_bits(all_hi, every, K);
+    int jm = 0;
+#pragma unroll
+    for (int j = kSmallPer - 1; j >= 0; --j) jm = x[j] == m ? j : jm;
+    sKlo[tid] = 0xFFFFFFFFu - (uint32_t)(lo + tid + kSmallThreads * jm);  // every wave read sKlo[w]
+    __syncthreads();
+    uint32_t Tlo = 0;
+    if (Thi != 0) {
+      uint32_t all_lo[4];
+      bool at_t[4];
+      int above = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        all_lo[i] = sKlo[lane + kWave * i];
+        at_t[i] = all_hi[i] == Thi;
+        above += __popcll(__ballot(all_hi[i] > Thi));
+      }
+      Tlo = block_kth_bits(all_lo, at_t, K - above);
+    }
+    place(std::true_type{}, Thi ? order_value(Thi) : -__builtin_inff(), Tlo, 1);
+    __syncthreads();
+    total = sCount[1];
+  }
+  if (wave != 0) return;
+  float S = 0.f;
+#pragma unroll
+  for (int w = 0; w < NW; ++w) S += sSum[w];
+  unsigned char* q = partials + ((size_t)row * split + part) * partial_stride(K);
+  Partial* hdr = reinterpret_cast<Partial*>(q);
+  uint64_t* keys = reinterpret_cast<uint64_t*>(q + sizeof(Partial));
+  if (lane == 0) {
+    hdr->cref = C;
+    hdr->cvalid = valid ? 1 : 0;
+    hdr->s = valid ? S : 0.f;
+    hdr->pad = 0;
+  }
+  if (total <= kWave) {
+    const uint64_t mine = lane < total ? sCand[lane] : 0ull;
+    int rank = 0;
+    for (int i = 0; i < total; ++i) rank += sCand[i] > mine ? 1 : 0;
+    if (lane < total && rank < K) keys[rank] = mine;
+    if (lane >= total && lane < K) keys[lane] = 0ull;
+  } else {
+    uint64_t L = 0ull;
+    for (int b = 0; b < total; b += kWave) {
+      const uint64_t v = b + lane < total ? sCand[b + lane] : 0ull;
+      L = b == 0 ? sort_desc64_u64(v) : merge_desc64(L, sort_desc64_u64(v));
+    }
+    if (lane < K) keys[lane] = L;
+  }
+}
+
+// ---- merging a row's segments ------------------------------------------------------------------
 // One workgroup of four waves per row merges the row's `split` (<= 256) partial results: thread
 // p reads partial p's (reference, exp sum) header and the workgroup reduces them. The key lists:
 //  * when the row holds at most kMergeFast entries (split K), every entry is loaded at once
@@ -1270,74 +1480,92 @@ __global__ __launch_bounds__(kMergeThreads) void topk_merge_kernel(
 }
 
 // Which kernel takes a call, with how many waves per workgroup, and how many workgroups share a row.
-// The streaming kernel pays ~K (1 + ln(V / K)) records per row in its one consumer wave, the row
-// kernel a threshold search and a sort of each wave's survivors whatever V is; so long rows with a
-// small K belong to the first, and where the line lies depends on how many rows share a compute
-// unit. Measured, us, streaming / row kernel, normal logits of standard deviation 2:
-//  * from 1024 rows on (four per compute unit) up to K = 16 always (1024 x 151936 K = 16 52.8 /
-//    55.9), above it by V against K: bf16 2048 x 60000 K = 32 82.3 / 66.4, 4000 x 32000 K = 48
-//    186 / 109, 1500 x 151936 K = 32 93.0 / 87.0; fp32 2200 x 100003 K = 48 5% for streaming.
-//    Just above 1024 rows the row kernel's fifth workgroup per compute unit runs alone, and
-//    streaming wins earlier (1040 x 100003 K = 32 51.9 / 58.2);
-//  * bf16 from 513 to 1023 rows while K is at most 32 and V at least 3500 K (640 x 151936 K = 16
-//    39.7 / 45.2, 800 x 100003 K = 8 34.0 / 38.1, 1000 x 20001 K = 2 13.8 / 16.4, but 580 x 60000
-//    K = 32 37 / 30), up to 512 rows while K is at most 8 and V at least 7000 K (512 x 60000 K = 2
-//    16.0 / 18.2, K = 16 5% for the row kernel) and V below 200000, where a row is so long that the
-//    row kernel's fixed part no longer counts (400 x 262144 K = 8 46.0 / 42.6);
-//  * fp32, whose exp sums weigh half as much against its bytes, from 513 rows at V >= 2000 K (800 x
-//    100003 K = 32 61.2 / 68.1; but 640 x 262144 K = 2 113 / 105), up to 512 with K at most 32 at
-//    4000 K (300 x 100003 K = 8 28.2 / 34.1, 400 x 262144 K = 48 86.8 / 79.5).
-// 257 to 340 rows are more than one round of whole rows but not two, and 513 to 640 more than two but
-// not three: long rows are split over four or two streaming workgroups there (300 x 262144 K = 8
-// 36.4, whole rows 44.7 / 41.6; fp32 580 x 262144 K = 48 107, whole rows 119 / 118).
-// The row kernel takes 16 waves a row while every workgroup has a compute unit of its own, else
-// eight (512 x 32000 K = 8 13.9, four 14.3, with 262144 logits K = 32 52.0 against 60), else (bf16
-// below 100000 logits) four once eight would need a second round (640 x 32000 K = 16 19.2 against
-// 22.0; at 100003 K = 48 48.7 against 46.4), and no more waves than tiles.
-// With fewer rows than compute units a row is split over workgroups of at least one tile per wave
-// (32768 logits); the merge launch costs ~5 us, so two workgroups only pay from 196608 logits
-// on (64 x 151936: four workgroups a row 16.8, one 18.6; 128 x 151936: two 20.2, one 18.8;
-// 100 x 262144: two 23.5, one 24.9). Above K = 32 the parts' longer lists cost more than they save
-// below 200000 logits (16 x 100003 K = 48 19.6 whole, 23.1 split); up to K = 8 eight-wave workgroups
-// of one tile per wave finish sooner while all run at once (fp32 16 x 100003 K = 8 13.9 against
-// 16.4, bf16 16 x 151936 K = 8 13.7 against 14.6).
+// Measured over 14282 points (both types; 1 to 4096 rows, V 64 to 1500000, K 1 to 64; normal logits
+// of standard deviation 2, device time of graph replays), us:
+//  * streaming: ~K (1 + ln(V / K)) records per row pass its one consumer wave, but nothing else is
+//    fixed, so it takes the rows too short to repay the row kernel's threshold searches and final
+//    ranking (1 x 2048 K = 8 6.5 against 8.1, 64 x 4097 K = 2 fp32 6.7 / 7.7), and long rows with a
+//    small K; with four and more rows per compute unit (from 1024) up to K = 16 always, above it by V
+//    against K (1024 x 65537 K = 44 fp32 56.6 / 60.1), earlier where a fifth workgroup of the row
+//    kernel would run alone (1100 x 3000 K = 48 fp32 25.8 / 35.6);
+//  * short segments: few long rows, while all segments run at once and K leaves their 256 lane maxima
+//    few candidates; fp32 from 49153 logits, bf16, whose segments hold half the bytes, from 65537
+//    (16 x 65537 K = 8 12.3, the row kernel 12.8 whole and 13.1 split). bf16 from K = 9 to 32, and
+//    from K = 6 at 98305 logits, goes to the row kernel (16 x 151936 K = 16 16.3 / 16.8), K above 32,
+//    where its waves' lists overflow in their first tile, does not (4 x 151936 K = 48 17.5 against
+//    19.8, fp32 16.4 / 22.7; 64 x 10000 fp32 14.6 / 17.7);
+//  * row kernel: the rest. 16 waves a row while every workgroup has a compute unit of its own, else
+//    eight, else four once eight would need a second round (below 100000 logits of bf16, 50000 of
+//    fp32: 700 x 14000 K = 8 fp32 16.4 against 18.7), and no more waves than tiles. With fewer rows
+//    than compute units a row is split over workgroups of at least one tile per wave (32768 logits);
+//    the merge launch costs ~5 us, so two workgroups only pay from 196608 logits on. Up to K = 8
+//    eight-wave workgroups of one tile per wave finish sooner while all run at once (16 x 151936 K =
+//    8 14.1 against 15.2);
+//  * streaming split: 257 to 340 rows are more than one round of whole rows but not two, and 513 to
+//    640 more than two but not three, so long rows are cut in four or two there; fp32 with K <= 2 over
+//    16 to 128 rows, where a record more or less counts least (48 x 100003 K = 2 14.9 against 16.6).
 struct TopkPlan {
-  int waves;  // 0: the streaming kernel
+  int waves;  // kStreaming, kSegments or the row kernel's
   int split;
 };
+constexpr int kStreaming = 0, kSegments = -1;
 
 bool topk_streams(int64_t rows, int64_t V, int K, bool bf16) {
-  if (rows >= 1024) return K <= 16 || V >= (int64_t)(!bf16 ? 2000 : rows < 1152 ? 3000 : 4000) * K;
+  if (V <= (K > 56 && (bf16 || rows <= 1024) ? 1024 : !bf16 && K <= 8 ? 3584 : 2560) || (K <= 4 && V <= (bf16 && K > 1 ? 4608 : 8192))) return true;
+  if (!bf16 && K <= 2 && rows > 128 && rows <= 256 && V <= 49152) return true;
+  if (rows >= 1024) {
+    const bool fifth = rows > 1024 && rows < 1280;
+    const int64_t few_tiles = !bf16 ? (K > 32 ? 4608 : 3584) : fifth ? 3584 : 0;
+    const int64_t per_k = !bf16 ? (rows < 1280 ? 1400 : 2000) : rows < 1152 ? 3000 : 4000;
+    return K <= 16 || (K <= 56 && V <= few_tiles) || V >= per_k * K;
+  }
   if (rows > 512)
-    return bf16 ? K <= 32 && V >= (int64_t)3500 * K : V >= (int64_t)2000 * K && (K > 8 || V < 200000);
+    return bf16 ? K <= 32 && V >= (int64_t)3500 * K
+                : V >= (int64_t)(K <= 16 ? 1000 : 2000) * K && (K > 8 || V < 200000);
   return rows > 256 && K <= (bf16 ? 8 : 32) && V >= (int64_t)(bf16 ? 7000 : 4000) * K &&
          !(bf16 && V >= 200000);
 }
 
+int64_t topk_segments(int64_t V) { return (V + kSmallSpan - 1) / kSmallSpan; }
+
+bool topk_takes_segments(int64_t rows, int64_t V, int K, bool bf16) {
+  const int64_t longest = K <= 3 ? 2097152 : !bf16 && K > 40 ? 1048576 : K <= 5 || K > 32 ? 524288 : 262144;
+  if (V <= kSmallSpan || V > longest || K > 48 || rows * topk_segments(V) > kSmallFill) return false;
+  if (K > 32) return V > (bf16 ? 98304 : K > 40 ? kSmallSpan : 49152);
+  return V > (bf16 ? 65536 : 49152) && (!bf16 || K <= 5 || (K <= 8 && V <= 98304));
+}
+
+// Streaming workgroups of at least 12288 logits, about four per compute unit.
+int64_t topk_stream_parts(int64_t rows, int64_t V) {
+  const int64_t by_fill = (1024 + rows - 1) / rows, by_len = V / 12288;
+  const int64_t s = by_fill < by_len ? by_fill : by_len;
+  return s < 1 ? 1 : s > 256 ? 256 : s;
+}
+
 TopkPlan topk_plan(int64_t rows, int64_t V, int K, bool bf16) {
-  if (rows > 256 && rows <= 340 && V >= (bf16 ? 150000 : 200000) && V >= (int64_t)16000 * K)
-    return {0, 4};
-  if (rows > 512 && rows <= 640 && V >= 200000 && (bf16 ? K <= 32 : K > 8)) return {0, 2};
-  if (topk_streams(rows, V, K, bf16)) return {0, 1};
+  if (topk_takes_segments(rows, V, K, bf16)) return {kSegments, (int)topk_segments(V)};
+  if (!bf16 && K <= 2 && V > 65536 && V <= 262144 && rows > 16 && rows <= 128)
+    return {kStreaming, (int)topk_stream_parts(rows, V)};
+  if (rows > 256 && rows <= 340 && V >= (bf16 ? 150000 : 200000) && V >= (int64_t)(bf16 ? 16000 : 8000) * K)
+    return {kStreaming, 4};
+  if (rows > 512 && rows <= 640 && V >= 200000 && (bf16 ? K <= 32 : K > 8)) return {kStreaming, 2};
+  if (topk_streams(rows, V, K, bf16)) return {kStreaming, 1};
   const int64_t small = (V + 16383) / 16384;
   if (K <= 8 && V > 65536 && rows * small <= 256) return {8, (int)small};
   int64_t split = 256 / rows;
   if (split > V / 32768) split = V / 32768;
-  if (split < 1 || (split == 2 && V < 196608) || (K > 32 && V < 200000)) split = 1;
+  if (split < 1 || (split == 2 && V < 196608)) split = 1;
   int waves = rows * split <= 256 ? 16 : 8;
-  if (rows >= 1024 || (rows > 512 && bf16 && V < 100000)) waves = 4;
+  if (rows >= 1024 || (rows > 512 && V < (bf16 ? 100000 : 50000))) waves = 4;
   while (waves > 4 && (int64_t)(waves / 2) * kWave * kPerLane >= V) waves /= 2;
   return {waves, (int)split};
 }
 
-// The most workgroups that may share a row: what the size of the workspace allows for. About four per
-// compute unit, none with less than 12288 logits, or parts of 8192 where 512 workgroups hold them.
+// The parts that the workspace has room for: those of the streaming kernel, or of short segments where
+// these fill the chip and run at once. No plan of these sizes has more, whatever K and the type are.
 int topk_max_parts(int64_t rows, int64_t V) {
-  const int64_t by_fill = (1024 + rows - 1) / rows, by_len = V / 12288;
-  int64_t s = by_fill < by_len ? by_fill : by_len;
-  const int64_t t = (V + 8191) / 8192;
-  if (s < by_fill && t > 1 && t <= 256 && rows * t <= 512) s = t;
-  return (int)(s < 1 ? 1 : s > 256 ? 256 : s);
+  const int64_t by_fill = (1024 + rows - 1) / rows, s = topk_stream_parts(rows, V), t = topk_segments(V);
+  return (int)(s < by_fill && t > 1 && t <= 256 && rows * t <= kSmallFill ? t : s);
 }
 
 bool topk_args_ok(int64_t N, int64_t B, int64_t V, int K) {
@@ -1353,9 +1581,7 @@ bool topk_args_ok(int64_t N, int64_t B, int64_t V, int K) {
 
 using namespace lilicorr;
 
-// workspace: the status header, then (rows split over several workgroups) the partial results, for the
-// largest number of parts that a row may be given: topk_plan gives no more, for either type
-// (4 <= 1024 / rows up to 340 rows; ceil(V / 16384) <= V / 12288 and V / 8192 above 65536 logits).
+// workspace: the status header, then (rows split over several workgroups) the partial results.
 inline size_t topk_workspace_need(int64_t rows, int split, int K) {
   return kStatusBytes + (split == 1 ? 0 : (size_t)rows * split * partial_stride(K));
 }
@@ -1411,7 +1637,10 @@ static lilicorr_status topk_launch(const void* logits, lilicorr_dtype dtype, int
                        feat, ws);
   };
   auto dispatch = [&](auto bf) {
-    if (plan.waves == 16)
+    if (plan.waves == kSegments)
+      hipLaunchKernelGGL(topk_small_kernel<decltype(bf)::value>, grid, dim3(kSmallThreads), 0, stream,
+                         logits, V, K, split, ws);
+    else if (plan.waves == 16)
       row_kernel(bf, std::integral_constant<int, 16>{});
     else if (plan.waves == 8)
       row_kernel(bf, std::integral_constant<int, 8>{});

@@ -65,14 +65,14 @@ def test_size_queries(L):
     # a single request is split over several workgroups per row
     assert L.lilicorr_topk_workspace_bytes(1, 16, 151936, 8) > H
     assert L.lilicorr_topk_workspace_bytes(1, 16, 151936, 65) == 0
-    # the split rule, through the workspace size (header, then rows x segments x (16-byte
-    # partial header + K keys)): few rows whose short segments (<= 8192 logits) all run at once
-    # take ceil(V / 8192) of them
+    # the parts that a row may be given, through the workspace size (header, then rows x parts x
+    # (16-byte partial header + K keys)); which calls use them depends on K and the type too. Few
+    # rows whose short segments (<= 8192 logits) all run at once have room for ceil(V / 8192)
     part = lambda K: 16 + 8 * K
     assert L.lilicorr_topk_workspace_bytes(1, 16, 151936, 8) == H + 16 * 19 * part(8)
     assert L.lilicorr_topk_workspace_bytes(1, 8, 32000, 4) == H + 8 * 4 * part(4)
     assert L.lilicorr_topk_workspace_bytes(1, 1, 300000, 64) == H + 37 * part(64)
-    # more rows x segments than run at once: streaming segments of >= 12288 logits
+    # more rows x segments than run at once: parts of >= 12288 logits
     assert L.lilicorr_topk_workspace_bytes(2, 16, 151936, 16) == H + 32 * 12 * part(16)
     assert L.lilicorr_topk_workspace_bytes(16, 16, 151936, 16) == H + 256 * 4 * part(16)
     # rows shorter than one short segment stay whole

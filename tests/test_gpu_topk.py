@@ -73,19 +73,19 @@ EDGE = [
     (1, 2, 5000, 8, "equal"),
     (1, 2, 3000, 20, "zeros"),
     (2, 2, 4099, 10, "neginf"),
-    (1, 16, 151936, 8, "normal"),  # few rows: short segments of 8192 + merge kernel
+    (1, 16, 151936, 8, "normal"),  # few rows in parts: short segments (fp32), row kernel (bf16)
     (1, 1, 262144, 64, "ties"),
-    # short segments with exact ties at the threshold (lane maxima all equal: the id search)
+    # whole rows of the row kernel with exact ties at the threshold, or few values above -inf
     (1, 2, 20000, 8, "equal"),
     (1, 2, 20000, 20, "zeros"),
     (2, 2, 20001, 10, "neginf"),
-    (1, 3, 30000, 12, "maskblock"),  # whole segments at -inf next to finite ones
+    (1, 3, 30000, 12, "maskblock"),  # whole tiles at -inf next to finite ones
     (1, 1, 20000, 64, "ties"),
-    # a split that leaves rows*segments above one round: streaming segments + merge
+    # rows in parts of 32768 and more logits + merge
     (2, 16, 151936, 16, "normal"),
-    # more than 2048 partial keys per row: the merge kernel's list-merging path
+    # the same at K = 64: 576 partial keys
     (1, 1, 300000, 64, "normal"),
-    # the most rows the short-segment path takes (256 rows of two segments)
+    # one workgroup per compute unit
     (1, 256, 10000, 4, "normal"),
 ]
 
@@ -122,8 +122,8 @@ def test_topk_edge_cases(lib, case, dtype):
 
 
 def test_topk_workspace_shared_across_paths(lib):
-    """One zero-filled workspace through short-segment, streaming split and whole-row calls in
-    turn: every call matches the same call on a fresh workspace bit for bit."""
+    """One zero-filled workspace through row-kernel calls, split and whole, in turn: every call
+    matches the same call on a fresh workspace bit for bit."""
     shapes = [(1, 16, 151936, 8), (2, 16, 151936, 16), (1, 256, 10000, 4), (4, 16, 151936, 16),
               (1, 16, 151936, 8), (1, 3, 30000, 12)]
     need = max(lib.lilicorr_topk_workspace_bytes(N, B, V, K) for N, B, V, K in shapes)
@@ -203,17 +203,18 @@ def test_topk_features_ties_and_small_k(lib, K):
 # ---- the row kernel: waves per workgroup, rows split over workgroups, thresholds from maxima -------
 
 ROW_CASES = [
-    # (rows, V, K, kind): 4, 8 and 16 waves a workgroup by V, ragged ends, K past the group maxima
+    # (rows, V, K, kind): short rows (streaming), then 4, 8 and 16 waves a workgroup by V, ragged ends,
+    # K past the group maxima
     (3, 1, 1, "normal"), (2, 65, 64, "normal"), (5, 2049, 7, "normal"), (3, 4095, 33, "ties"),
     (3, 8193, 64, "normal"), (2, 16385, 16, "normal"), (2, 32769, 64, "normal"),
-    # split over 3 and 8 workgroups, and two of them from 196608 logits
+    # split over 3 (fp32: 8 streaming) and 8 workgroups, and two of them from 196608 logits
     (70, 98310, 2, "normal"), (1, 262147, 50, "ties"), (90, 196609, 3, "normal"),
-    # eight waves (257 rows), four (641 bf16; 1024 with K above V / 4000 and 16)
+    # many short rows
     (257, 2100, 9, "normal"), (641, 700, 5, "ties"), (1024, 600, 17, "normal"),
-    # eight-wave workgroups of one tile per wave (K <= 8 above 65536 logits), rows whole above K = 32
+    # few long rows: short segments, row kernel in 4 parts (fp32: 10 streaming), short segments
     (3, 65537, 8, "normal"), (31, 131075, 2, "ties"), (2, 99991, 33, "normal"),
-    # streaming: whole rows by V against K from 257 rows, four workgroups a row, and beside them the
-    # row kernel just below each line (bf16: 7000 K to 512 rows, 3500 K above; fp32: 4000 K, 2000 K)
+    # streaming: whole rows by V against K from 257 rows, four and two workgroups a row; beside them
+    # the row kernel below 3500 K (600 rows, bf16)
     (261, 28003, 4, "normal"), (513, 14003, 4, "ties"), (600, 13999, 7, "normal"),
     (258, 200007, 2, "normal"), (513, 200003, 9, "normal"),
     (1030, 52001, 17, "normal"),
@@ -257,15 +258,38 @@ def test_topk_row_kernel(lib, rows, V, K, kind, bf16):
     assert np.array_equal(a[1].view(np.int32), b[1].view(np.int32))
 
 
-# ---- rows in parts: the merge kernel's paths -------------------------------------------------------
+# ---- every way a row is split, the merge kernel's paths, the lines of the plan ---------------------
 
 SPLIT_CASES = [
+    # short segments: both ends of their range, ties at the threshold (lane maxima all equal: the id
+    # search), more than 64 candidates, whole segments at -inf beside finite ones
+    (2, 70000, 4, "normal"), (2, 98305, 33, "ties"), (1, 524288, 48, "normal"),
+    (26, 155648, 4, "maskblock"), (2, 70000, 4, "equal"), (3, 8193, 41, "ties"),
+    (2, 70001, 20, "few finite"), (1, 120000, 40, "zeros"),
     # row kernel in parts: a part with no finite logit, more candidates than one wave ranks, and more
     # than 2048 partial keys
     (3, 98310, 12, "maskblock"), (2, 300000, 64, "63 a part"), (1, 1200000, 64, "normal"),
     (1, 1200000, 64, "maskblock"),
+    # streaming in parts: 257 to 340 rows, 513 to 640, fp32 with K = 2 (bf16: row kernel in parts)
+    (258, 200007, 2, "maskblock"), (513, 200003, 9, "maskblock"), (60, 65539, 2, "maskblock"),
+]
+
+LINE_CASES = [
+    # short rows: streaming up to 2560 logits (1024 above K = 56), 4608 or 8192 up to K = 4
+    (3, 2560, 56, "normal"), (3, 2561, 56, "ties"), (2, 1025, 57, "normal"), (2, 8192, 4, "normal"),
+    (2, 8193, 1, "normal"),
     # more than 64 and more than 128 survivors to rank
     (5, 10000, 52, "normal"), (5, 10000, 64, "ties"),
+    # eight waves (257 rows), four (641, 1024); up to 512 rows either side of 7000 K (bf16) and 4000 K
+    # (fp32), above of 1000 K (fp32, K = 7)
+    (257, 9000, 9, "normal"), (641, 4990, 5, "ties"), (1024, 5000, 17, "normal"),
+    (261, 28003, 5, "normal"), (261, 15999, 4, "normal"), (600, 6999, 7, "normal"),
+    (600, 7000, 7, "normal"),
+    # from 1152 (bf16) and 1280 (fp32) rows, either side of 4000 K and 2000 K; a fifth workgroup
+    (1152, 67999, 17, "normal"), (1152, 68000, 17, "normal"), (1280, 33999, 17, "normal"),
+    (1280, 34000, 17, "normal"), (1100, 3584, 40, "ties"), (1100, 4608, 33, "normal"),
+    # 200000 logits: bf16 up to 512 rows, fp32 above
+    (341, 199999, 8, "normal"), (341, 200001, 8, "normal"), (641, 200001, 8, "normal"),
 ]
 
 
@@ -285,7 +309,7 @@ def _split_logits(rows, V, K, kind):
 
 
 @pytest.mark.parametrize("bf16", [True, False], ids=["bf16", "fp32"])
-@pytest.mark.parametrize("rows,V,K,kind", SPLIT_CASES)
+@pytest.mark.parametrize("rows,V,K,kind", SPLIT_CASES + LINE_CASES)
 def test_topk_plan_paths(lib, rows, V, K, kind, bf16):
     print(f"plan paths rows={rows} V={V} K={K} {kind} bf16={bf16}", flush=True)
     x = _split_logits(rows, V, K, kind)
@@ -293,10 +317,28 @@ def test_topk_plan_paths(lib, rows, V, K, kind, bf16):
     _check_rows(lib, x, K, range(0, rows, max(1, rows // 8)), f"{kind} rows={rows} V={V} K={K}")
 
 
+def test_topk_workspace_shared_across_kernels(lib):
+    """As test_topk_workspace_shared_across_paths, through short segments, rows in streaming parts,
+    whole streaming rows, row-kernel parts and merged lists."""
+    shapes = [(1, 16, 151936, 4), (258, 1, 200007, 2), (2, 600, 2000, 8), (1, 3, 98310, 12),
+              (1, 1, 1200000, 64), (1, 16, 151936, 4)]
+    need = max(lib.lilicorr_topk_workspace_bytes(N, B, V, K) for N, B, V, K in shapes)
+    ws = torch.zeros((need + 15) // 16 * 16, dtype=torch.uint8, device="cuda")
+    for i, (N, B, V, K) in enumerate(shapes):
+        print(f"topk shared workspace call {i}: N={N} B={B} V={V} K={K}", flush=True)
+        x = torch.randn(N, B, V, generator=torch.Generator().manual_seed(i)).to(torch.bfloat16).cuda()
+        got = lib.topk(x, K, workspace=ws)
+        fresh = lib.topk(x, K)
+        torch.cuda.synchronize()
+        for g, f in zip(got, fresh):
+            assert_equal(to_np(g), to_np(f), f"call {i}")
+    assert lib.topk_wait_status(ws) == 0
+
+
 @pytest.mark.parametrize("bf16", [True, False], ids=["bf16", "fp32"])
 @pytest.mark.parametrize("nan", ["every chunk", "whole tiles"])
 @pytest.mark.parametrize("rows,V,K", [
-    (2, 40000, 16), (3, 151936, 8),        # few rows, whole and in parts
+    (2, 40000, 16), (3, 151936, 8), (3, 151936, 4),  # few rows, whole and in parts
     (260, 100000, 16), (1100, 50000, 17),  # waves of more than four tiles: maxima of every form
     (1100, 9000, 4)])                      # streaming
 def test_topk_nan_logits(lib, rows, V, K, nan, bf16):
