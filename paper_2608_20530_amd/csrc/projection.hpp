@@ -48,7 +48,13 @@ struct VecGeom {
   int rm;     // 16-row blocks per workgroup of the candidate-vector kernel
 };
 
-// rm: 64-row tiles up to d = 512 (two workgroups per compute unit; at d <= 256 a 128-row tile's
+// rm: up to d = 256 a workgroup waits for its rows, for the weights that it streams whatever its
+// rows are, and for its stores, one after the other, so 16-row tiles for as long as more rows per
+// workgroup do not save more of the stream than they add to the chain, then 32-row ones (us, 16 / 32 /
+// 64 rows per tile: 128 rows at d = 64 5.0 / 7.2 / 11.8, at 256 8.2 / 11.1 / 17.6; 8192 rows at d = 64
+// 6.3 / 8.2 / 12.4, at 128 8.7 / 10.0 / 14.3, at 256 20.1 / 15.3 / 18.5; 13000 at 128 12.7 / 11.3 /
+// 16.2, at 256 30.3 / 24.5 / 21.8).
+// Else 64-row tiles up to d = 512 (two workgroups per compute unit; at d <= 256 a 128-row tile's
 // 8 x 4 accumulator blocks plus two weight buffers exceed the 256 registers of two waves per
 // SIMD and spilled: 175 against 160 us at 131072 rows, d = 256; at 256 < d <= 512 it needs 133 KB
 // of LDS, one workgroup per compute unit, and measured 7% slower at 131072 rows, d = 512);
@@ -60,8 +66,12 @@ inline VecGeom vec_geom(int d, int64_t M = 0) {
   g.dk = (d + 31) / 32;
   g.dkp = (g.dk + 1) / 2 * 2;
   g.waves = g.nbp / kNbPerWave;
-  (void)M;
-  g.rm = d > 512 ? 2 : 4;
+  if (d > 512)
+    g.rm = 2;
+  else if (d <= 256 && M * d <= 2200000)
+    g.rm = M * d <= 1048576 && M <= 32768 ? 1 : 2;
+  else
+    g.rm = 4;
   return g;
 }
 

@@ -21,6 +21,8 @@
 #include <math.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "common.hpp"
 #include "lilicorr.h"
 #include "projection.hpp"
@@ -600,27 +602,27 @@ void launch_vectors_f32(const int32_t* ids, const float* E, const unsigned char*
 }
 
 // Which kernels take a call. Whole rows per workgroup cost the latency of a side's whole weights
-// however few rows there are (bf16: 17 us at d = 256, 25 at 512, 68 at 1024; fp32 9, 17 and 70), so
-// while the tiles of vectors_split_kernel fit one round of compute units the smallest such tile is
-// taken (us, bf16, with the norm pass: 128 rows 6.1, 6.5 and 8.9; 512 rows at d = 512 9.6, at 1024
-// 17.2; 4096 rows at 256 16.4 against 18.3), for fp32 from d = 256 on, there up to 512 rows (1024
-// rows at 256: 11 against 9.9). The second launch is not worth it where the weights are a few kilobytes
-// (32 rows at d = 64 10.6 against 9.6), nor are 64 x 128 tiles that hold whole rows anyway (8192 rows at
-// d = 128 15.5 against 14.7). Above d = 768 the 1024-thread whole-row workgroups lose to 128 x 128
-// tiles at any row count (d = 1024, 2048 rows 37 against 63, 4096 64 against 72, 16384 236 against
-// 269); between 512 and 768 only while one round holds the tiles (4096 rows at 768: 48 against 41).
+// however few rows there are (bf16: 20 us at d = 320, 25 at 512, 68 at 1024; fp32 9 at 256, 17 and 70),
+// so above d = 256, while the tiles of vectors_split_kernel fit one round of compute units, the smallest
+// such tile is taken (us, bf16, with the norm pass: 128 rows 6.4, 6.5 and 8.9; 512 rows at d = 512 9.6,
+// at 1024 17.2), for fp32 from d = 256 on, there up to 512 rows (1024 rows at 256: 11 against 9.9). Below,
+// whole rows in 16-row tiles are as fast or nearly (d = 64 5.0 against 6.1, 128 5.8 / 6.1, 192 6.8 / 6.2, 256
+// 8.2 / 6.3 at 128 rows) and need no second launch, which costs an eager call 2.4 us of the host's time
+// (candidate_vectors in a loop, 8 to 3000 rows, 8.6 against 11.1). Above d = 768 the 1024-thread
+// whole-row workgroups lose to 128 x 128 tiles at any row count (d = 1024, 2048 rows 37 against 63, 4096
+// 64 against 72, 16384 236 against 269); between 512 and 768 only while one round holds the tiles (4096
+// rows at 768: 48 against 41).
 enum { kVecRows = 0, kVec16x32, kVec32x32, kVec32x64, kVec64x64, kVec64x128, kVecTiles };
 
 int vec_kernel(int64_t M, int64_t V, int d, bool f32) {
   if (V * d * (f32 ? 4 : 2) >= ((int64_t)1 << 31) || M >= ((int64_t)1 << 31)) return kVecRows;
   auto fits = [&](int bm, int bn) { return (M + bm - 1) / bm * ((d + bn - 1) / bn) * 2 <= 256; };
-  if (d <= 64 && M <= 64) return kVecRows;
-  if (!f32 || d > 256 || (d == 256 && M <= 512)) {
+  if (d > 256 || (f32 && d == 256 && M <= 512)) {
     if (fits(16, 32)) return kVec16x32;
     if (fits(32, 32)) return kVec32x32;
     if (fits(32, 64)) return kVec32x64;
     if (fits(64, 64)) return kVec64x64;
-    if (d > 128 && fits(64, 128)) return kVec64x128;
+    if (fits(64, 128)) return kVec64x128;
   }
   if (!f32 && (d > 768 || (d > 512 && fits(128, 128)))) return kVecTiles;
   return kVecRows;
@@ -718,21 +720,24 @@ extern "C" lilicorr_status lilicorr_candidate_vectors(const int32_t* ids, const 
                        (size_t)g.waves * rows_wg * sizeof(float) + (size_t)rows_wg * sizeof(int32_t);
     const dim3 grid((unsigned)nblk, 2), block(g.waves * kWave);
     const uint16_t* e16 = static_cast<const uint16_t*>(E);
-    if (g.rm == 4) {
-      static const hipError_t attr4 = hipFuncSetAttribute(
-          reinterpret_cast<const void*>(cand_vectors_mfma_kernel<4, 512>),
+    auto launch = [&](auto rm, auto threads) {
+      constexpr int RM = decltype(rm)::value, MAXT = decltype(threads)::value;
+      static const hipError_t attr = hipFuncSetAttribute(
+          reinterpret_cast<const void*>(cand_vectors_mfma_kernel<RM, MAXT>),
           hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      (void)attr4;
-      hipLaunchKernelGGL((cand_vectors_mfma_kernel<4, 512>), grid, block, lds, stream, ids, e16, p,
-                         M, V, d, g.nbp, g.dkp, in_vec, out_vec);
-    } else {
-      static const hipError_t attr2 = hipFuncSetAttribute(
-          reinterpret_cast<const void*>(cand_vectors_mfma_kernel<2, 1024>),
-          hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-      (void)attr2;
-      hipLaunchKernelGGL((cand_vectors_mfma_kernel<2, 1024>), grid, block, lds, stream, ids, e16, p,
-                         M, V, d, g.nbp, g.dkp, in_vec, out_vec);
-    }
+      (void)attr;
+      hipLaunchKernelGGL((cand_vectors_mfma_kernel<RM, MAXT>), grid, block, lds, stream, ids, e16, p, M,
+                         V, d, g.nbp, g.dkp, in_vec, out_vec);
+    };
+    typedef std::integral_constant<int, 512> Upto512;
+    if (d > 512)
+      launch(std::integral_constant<int, 2>{}, std::integral_constant<int, 1024>{});
+    else if (g.rm == 1)
+      launch(std::integral_constant<int, 1>{}, Upto512{});
+    else if (g.rm == 2)
+      launch(std::integral_constant<int, 2>{}, Upto512{});
+    else
+      launch(std::integral_constant<int, 4>{}, Upto512{});
   } else {
     const VecGeom g = vec_geom(d, M);
     const float* e32 = static_cast<const float*>(E);

@@ -47,7 +47,7 @@ def test_vectors_configs(lib, cfg_inputs, cfg_index):
     # padded column groups and k-blocks: d = 80 (5 -> 8 column blocks, 3 -> 4 k-blocks),
     # d = 272 (17 -> 20, 9 -> 10), d = 1008 (63 -> 64, 32)
     (80, 9, 3, 7, "bf16"), (272, 16, 2, 5, "bf16"), (1008, 4, 2, 3, "bf16"),
-    # enough rows for the 128-row tiles (M = 131072)
+    # enough rows for the 64-row tiles (M = 131072)
     (64, 32, 64, 64, "bf16"),
 ])
 def test_vectors_shapes(lib, d, K, N, B, e_dtype):
@@ -135,13 +135,15 @@ def test_vectors_f32_rows(lib, d, M):
 
 
 @pytest.mark.parametrize("e_dtype", ["bf16", "f32"])
-@pytest.mark.parametrize("d,M", [(16, 1), (64, 64), (128, 4097),  # whole rows beside the spread ones
-                                 (64, 65), (48, 1025), (240, 129), (256, 512),  # split tiles, 16 x 32 up
-                                 (272, 900), (512, 1023), (1008, 600), (1024, 1000),
+@pytest.mark.parametrize("d,M", [(16, 1), (64, 64), (128, 4097), (64, 65), (48, 1025), (240, 129),
+                                 (256, 4096), (128, 8200), (256, 8593), (64, 34400),  # whole rows
+                                 (256, 512), (272, 900), (512, 287), (528, 255),  # split tiles, 16 x 32 up
+                                 (512, 1023), (1008, 600), (1024, 1000),
                                  (528, 2100), (784, 4100), (1024, 2049)])  # 128 x 128 (bf16)
 def test_vectors_spread_columns(lib, d, M, e_dtype):
-    """Columns of a row spread over workgroups, rows scaled to unit norm by a second kernel: every
-    tile of the dispatch, ragged rows and columns, half-empty last k-blocks, ids outside the table.
+    """Columns of a row spread over workgroups, rows scaled to unit norm by a second kernel, and beside
+    them whole rows in tiles of 16, 32 and 64 (bf16 up to d = 256): every tile of the dispatch, ragged
+    rows and columns, half-empty last k-blocks, ids outside the table.
     A table row of infinities sits behind every row of the d % 32 == 16 cases: a read past a row's
     end would show. The bound is that of d fp32 additions, as above."""
     V = 400
