@@ -457,9 +457,8 @@ int compute_units() {
 // d = 64, 2.1e-7 at 192, 4.9e-7 at 1024 (fp32 FMA chains: 1.7e-7, 2.7e-7, 5.9e-7). A workgroup owns
 // 16 RM rows and all d columns of one side, each wave four 16-column blocks, the weights one block
 // at a time through four register buffers as in project_tile_lean. Bound: the weight stream from
-// L2 (3 KB per 8 RM matrix instructions), so two row blocks once they give every compute unit a
-// workgroup and their planes fit; with few rows it is latency, and one row block gives twice the
-// workgroups. (us, the FMA kernel before / this: 1920 rows at d = 192 25 / 9, 4096 at 256 44 / 16,
+// L2 (3 KB per 8 RM matrix instructions), so two row blocks for many rows, where their planes fit; with
+// fewer it is latency, and one row block is the shorter chain and twice the workgroups. (us, the FMA kernel before / this: 1920 rows at d = 192 25 / 9, 4096 at 256 44 / 16,
 // 40000 at 256 385 / 85, 8192 at 512 271 / 65, 4096 at 1024 1122 / 157.)
 constexpr int kF32Planes = 3;
 
@@ -742,9 +741,10 @@ extern "C" lilicorr_status lilicorr_candidate_vectors(const int32_t* ids, const 
     const VecGeom g = vec_geom(d, M);
     const float* e32 = static_cast<const float*>(E);
     if ((M + 15) / 16 > 0x7fffffffll) return LILICORR_ERR_UNSUPPORTED;
-    // two row blocks once they give every compute unit a workgroup (above d = 768 their three
-    // planes do not fit in LDS)
-    const bool two = (M + 31) / 32 * 2 >= 256 && d <= 768;
+    // two row blocks once the rows outweigh the longer chain of a tile (us, one / two: 4096 rows at d =
+    // 32 6.6 / 9.3, at 512 38.6 / 33.3; 16384 at 128 13.5 / 15.1, 24576 23.4 / 18.7; at d = 64 one wins up
+    // to 131072 rows); above d = 768 their three planes do not fit in LDS
+    const bool two = d > 64 && d <= 768 && M * d >= 2000000;
     if (g.waves > 8 && two)
       launch_vectors_f32<2, 1024>(ids, e32, p, M, V, d, g, in_vec, out_vec, stream);
     else if (g.waves > 8)

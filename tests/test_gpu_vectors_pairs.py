@@ -105,9 +105,9 @@ def test_vectors_persistent_tiles(lib, d, N, B, K):
     assert (giv[0] == 0).all() and (giv[M - 1] == 0).all()
 
 
-@pytest.mark.parametrize("d,M", [(16, 15), (80, 17), (528, 33), (1024, 16),    # one row block
-                                 (48, 4065), (512, 4100), (560, 4100), (768, 4079),  # two
-                                 (784, 4100)])
+@pytest.mark.parametrize("d,M", [(16, 15), (80, 17), (48, 4065), (768, 2590), (784, 4100),  # one row block
+                                 (528, 33), (1024, 16),  # columns spread
+                                 (512, 4100), (560, 4100), (768, 4079), (128, 15700), (80, 25001)])  # two
 def test_vectors_f32_rows(lib, d, M):
     """fp32 embeddings: one and two 16-row blocks per workgroup, up to and above 512 threads, ragged
     rows, ids outside the table. The sums are fp32 over exact products of bf16 terms: the bound is
