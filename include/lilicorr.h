@@ -122,7 +122,9 @@ lilicorr_status lilicorr_topk_features(const void *logits, lilicorr_dtype dtype,
  *
  * lilicorr_candidate_vectors
  *   ids       [N][B][K] int32 (as produced by step 1); an id outside [0, V) gives zero vectors.
- *   E         [V][d] embedding table in `e_dtype` (bf16 uses matrix cores; fp32 uses vector FMA).
+ *   E         [V][d] embedding table in `e_dtype`. Both run on the bf16 matrix cores with fp32
+ *             accumulation: bf16 rows as they are, fp32 rows split exactly into three bf16 terms like
+ *             the weights (the product of the two smallest terms, below 2^-30, is left out).
  *   packed_w  buffer filled by lilicorr_pack_weights for the same d.
  *   in_vec, out_vec  [N][B][K][d] fp32 out.
  */
@@ -438,8 +440,9 @@ typedef struct {
     const float *g_attn, *g_ffn, *dist_bias, *same_bias;
 } lilicorr_scorer_layer;
 
-/* Bytes of one packed layer (weights transposed for the matrix cores, gains, biases) for these
- * sizes; 0 if the sizes are unsupported. */
+/* Bytes of one packed layer (weights in the matrix cores' operand order, gains, biases) for these
+ * sizes; 0 if the sizes are unsupported. The layout belongs to the library that wrote it: pack again
+ * rather than keep packed buffers from one version to the next. */
 size_t lilicorr_scorer_packed_bytes(int H, int heads, int F, int64_t S);
 
 /* Packs one layer into `packed` (device, 16-byte aligned, lilicorr_scorer_packed_bytes bytes,

@@ -8,7 +8,7 @@
 //   [side 2][k-block dkp][term 3][column block nbp][lane 64][8 bf16]: v_mfma_f32_16x16x32_bf16
 //     B fragments; lane l of block (kb, nb) holds W[kb*32 + (l/16)*8 + i][nb*16 + l%16], i = 0..7
 //     (0 for rows or columns at or beyond d)
-//   followed by [side 2][d][d] fp32 copies (used by the fp32-embedding kernel)
+//   followed by [side 2][d][d] fp32 copies (read by the certified passes, which re-score in double)
 // Side 0 is W_in, side 1 is W_out. nbp is d/16 rounded up to whole wave column groups and dkp is
 // the number of 32-deep k-blocks rounded up to even, so the MFMA loop never branches.
 #pragma once

@@ -157,7 +157,7 @@ __device__ __forceinline__ void tile_of(int64_t M, int ntn, int BM, int64_t& tm,
 // the L1/L2 into one of four register buffers, three k-blocks ahead. Only A in LDS: with both
 // operands there, 12 KB of LDS reads per 32 MFMAs and wave plus the copies ask for more than the
 // 128 bytes a cycle that LDS gives (the four products at M = 15360, H = 1024, F = 2048 took 112,
-// 47, 76 and 88 us that way and take 90, 45, 64 and 66 now; the loop alone runs at 1.6 PFLOP/s,
+// 47, 76 and 88 us that way and take 90, 47, 64 and 70 now; the loop alone runs at 1.6 PFLOP/s,
 // and what is left is the first loads, the output and, for the residual, 126 MB of X that no
 // product runs beside: one round of tiles). 256 x 256 tiles of eight waves, one workgroup per
 // compute unit, took 112, 48, 67 and 69 us with the products alone.
