@@ -169,7 +169,7 @@ def _features(lib, logits_cpu, K):
 @pytest.mark.parametrize("cfg_index", [0, 1, 2, 3, 4])
 def test_topk_features_configs(lib, cfg_inputs, oracle_chain, cfg_index):
     """ids / logp as lilicorr_topk gives them; features against the oracle's from its own top-K
-    (configs 0-1 split each row over several workgroups: the merge kernel writes them)."""
+    (config 1 splits each row over several workgroups: the merge kernel writes them)."""
     cfg, inp = cfg_inputs(cfg_index)
     print(f"features config {cfg_index} {cfg.name}", flush=True)
     gi, gl, gf = _features(lib, inp["logits"], cfg.K)
